@@ -60,45 +60,45 @@ int uneven_blocks_per_cu(int mode) {
 }
 
 template <int L, int PLAN>
-static void geo(int &entries, int &passes, int *rad) {
+static void geo(bool merged, int &entries, int &passes, int *rad) {
   typedef Geometry<L, PLAN> G;
-  entries = G::tw_entries();
+  entries = G::tw_entries(merged);
   passes = G::S::P;
   for (int p = 0; p < 4; ++p) rad[p] = G::radix(p);
 }
 
 template <int PLAN>
-static void geometry_plan(int log2n, int &entries, int &passes, int *rad) {
+static void geometry_plan(int log2n, bool merged, int &entries, int &passes, int *rad) {
   switch (log2n) {
-    case 3: geo<3, PLAN>(entries, passes, rad); return;
-    case 4: geo<4, PLAN>(entries, passes, rad); return;
-    case 5: geo<5, PLAN>(entries, passes, rad); return;
-    case 6: geo<6, PLAN>(entries, passes, rad); return;
-    case 7: geo<7, PLAN>(entries, passes, rad); return;
-    case 8: geo<8, PLAN>(entries, passes, rad); return;
-    case 9: geo<9, PLAN>(entries, passes, rad); return;
-    case 10: geo<10, PLAN>(entries, passes, rad); return;
-    case 11: geo<11, PLAN>(entries, passes, rad); return;
-    case 12: geo<12, PLAN>(entries, passes, rad); return;
-    case 13: geo<13, PLAN>(entries, passes, rad); return;
-    case 14: geo<14, PLAN>(entries, passes, rad); return;
+    case 3: geo<3, PLAN>(merged, entries, passes, rad); return;
+    case 4: geo<4, PLAN>(merged, entries, passes, rad); return;
+    case 5: geo<5, PLAN>(merged, entries, passes, rad); return;
+    case 6: geo<6, PLAN>(merged, entries, passes, rad); return;
+    case 7: geo<7, PLAN>(merged, entries, passes, rad); return;
+    case 8: geo<8, PLAN>(merged, entries, passes, rad); return;
+    case 9: geo<9, PLAN>(merged, entries, passes, rad); return;
+    case 10: geo<10, PLAN>(merged, entries, passes, rad); return;
+    case 11: geo<11, PLAN>(merged, entries, passes, rad); return;
+    case 12: geo<12, PLAN>(merged, entries, passes, rad); return;
+    case 13: geo<13, PLAN>(merged, entries, passes, rad); return;
+    case 14: geo<14, PLAN>(merged, entries, passes, rad); return;
   }
   entries = passes = 0;
 }
 
-static void geometry(int log2n, int plan, int &entries, int &passes, int *rad) {
-  if (plan == 1) geometry_plan<1>(log2n, entries, passes, rad);
-  else geometry_plan<0>(log2n, entries, passes, rad);
+static void geometry(int log2n, int plan, bool merged, int &entries, int &passes, int *rad) {
+  if (plan == 1) geometry_plan<1>(log2n, merged, entries, passes, rad);
+  else geometry_plan<0>(log2n, merged, entries, passes, rad);
 }
 
-int twiddle_entries(int log2n, int plan) {
+int twiddle_entries(int log2n, int plan, bool merged) {
   int e, p, r[4];
-  geometry(log2n, plan, e, p, r);
+  geometry(log2n, plan, merged, e, p, r);
   return e;
 }
 int pass_count(int log2n, int plan) {
   int e, p, r[4];
-  geometry(log2n, plan, e, p, r);
+  geometry(log2n, plan, false, e, p, r);
   return p;
 }
 bool second_plan(int log2n) { return has_second_plan(log2n); }
@@ -123,7 +123,7 @@ int threads_per_transform(int log2n) {
 
 int pass_radix(int log2n, int plan, int q) {
   int e, p, r[4];
-  geometry(log2n, plan, e, p, r);
+  geometry(log2n, plan, false, e, p, r);
   return (q >= 0 && q < 4) ? r[q] : 0;
 }
 

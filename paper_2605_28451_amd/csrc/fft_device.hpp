@@ -15,6 +15,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace bfp {
 
 typedef _Float16 f16;
@@ -41,36 +43,7 @@ __device__ __forceinline__ c32 cmul(c32 a, c32 b) {
   BFP_NO_CONTRACT
   return c32{__builtin_fmaf(a.x, b.x, -(a.y * b.y)), __builtin_fmaf(a.x, b.y, a.y * b.x)};
 }
-__device__ __forceinline__ c32 cscale(c32 a, float s) {
-  BFP_NO_CONTRACT
-  return c32{a.x * s, a.y * s};
-}
 __device__ __forceinline__ c32 cconj(c32 a) { return c32{a.x, -a.y}; }
-__device__ __forceinline__ c32 mul_mi(c32 a) { return c32{a.y, -a.x}; }   // x (-i)
-__device__ __forceinline__ c32 mul_pi(c32 a) { return c32{-a.y, a.x}; }   // x (+i)
-__device__ __forceinline__ c32 cneg(c32 a) { return c32{-a.x, -a.y}; }
-// x (c + i s) with compile-time constants
-__device__ __forceinline__ c32 cmulk(c32 a, float c, float s) {
-  BFP_NO_CONTRACT
-  return c32{__builtin_fmaf(a.x, c, -(a.y * s)), __builtin_fmaf(a.x, s, a.y * c)};
-}
-// x k (1 - i), x k (-1 - i), x k (-1 + i), x k (1 + i)
-__device__ __forceinline__ c32 mul_1mi(c32 a, float k) {
-  BFP_NO_CONTRACT
-  return c32{(a.x + a.y) * k, (a.y - a.x) * k};
-}
-__device__ __forceinline__ c32 mul_m1mi(c32 a, float k) {
-  BFP_NO_CONTRACT
-  return c32{(a.y - a.x) * k, -(a.x + a.y) * k};
-}
-__device__ __forceinline__ c32 mul_m1pi(c32 a, float k) {
-  BFP_NO_CONTRACT
-  return c32{-(a.x + a.y) * k, (a.x - a.y) * k};
-}
-__device__ __forceinline__ c32 mul_1pi(c32 a, float k) {
-  BFP_NO_CONTRACT
-  return c32{(a.x - a.y) * k, (a.x + a.y) * k};
-}
 
 // ----------------------------------------------------- packed FP16 ops ---
 __device__ __forceinline__ h2 cadd(h2 a, h2 b) { return a + b; }
@@ -86,18 +59,7 @@ __device__ __forceinline__ h2 cmul(h2 a, h2 b) {
   const h2 t = h2{-a.y, a.x} * h2{b.y, b.y};
   return __builtin_elementwise_fma(a, h2{b.x, b.x}, t);
 }
-__device__ __forceinline__ h2 cscale(h2 a, float s) { return a * h2{(f16)s, (f16)s}; }
 __device__ __forceinline__ h2 cconj(h2 a) { return h2{a.x, -a.y}; }
-__device__ __forceinline__ h2 mul_mi(h2 a) { return h2{a.y, -a.x}; }
-__device__ __forceinline__ h2 mul_pi(h2 a) { return h2{-a.y, a.x}; }
-__device__ __forceinline__ h2 cneg(h2 a) { return -a; }
-__device__ __forceinline__ h2 cmulk(h2 a, float c, float s) {
-  return cmul(a, h2{(f16)c, (f16)s});
-}
-__device__ __forceinline__ h2 mul_1mi(h2 a, float k) { return (a + h2{a.y, -a.x}) * h2{(f16)k, (f16)k}; }
-__device__ __forceinline__ h2 mul_m1mi(h2 a, float k) { return (h2{a.y, -a.x} - a) * h2{(f16)k, (f16)k}; }
-__device__ __forceinline__ h2 mul_m1pi(h2 a, float k) { return (h2{-a.y, a.x} - a) * h2{(f16)k, (f16)k}; }
-__device__ __forceinline__ h2 mul_1pi(h2 a, float k) { return (a + h2{-a.y, a.x}) * h2{(f16)k, (f16)k}; }
 
 // Exact power-of-two scaling a . 2^-K (the block-floating-point shift) as an
 // ldexp instruction: exact for normal results, round-to-nearest-even into
@@ -142,65 +104,285 @@ __device__ __forceinline__ h2 conj_pow2(h2 a) {
   else return pk_scale(a, h2{(f16)(1.0f / (1 << K)), (f16)(-1.0f / (1 << K))});
 }
 
-// ------------------------------------------------- radix constants ------
-// cos(pi/4), cos(pi/8), sin(pi/8) to 20 significant digits.
+// ----------------------------------------------------- butterflies ------
+// (a, b) -> (a + w b, a - w b), every operation an explicit FMA (contraction
+// off), so every kernel gets the same bits.  NEGI takes -i w for w (a swap of
+// components and a sign, free as operand selects), CJ returns the conjugated
+// results (signs only).  The forms differ in how w is given:
+//   bf_one   w = 1 (or -i): additions;
+//   bf_tan   w = g (1 + i t), |t| <= 1 (COS), or w = g (t + i) (!COS):
+//            u = b + t (i b) (or t b + i b), then a +- g u: 6 FMAs on FP32
+//            pairs and 3 on packed FP16, against 8 and 4 for a product and
+//            two sums, with one rounding less;
+//   bf_fma   w = (re, im): a +- w b, 8 (4) FMAs;
+//   bf_twice w = (re, im): s = a + w b, then 2 a - s: 6 (3), one rounding
+//            more on the difference.
+template <bool NEGI, bool CJ, class C>
+__device__ __forceinline__ void bf_one(C &a, C &b) {
+  const C p = CJ ? cconj(a) : a, q = CJ ? cconj(b) : b;
+  if constexpr (!NEGI) {
+    a = cadd(p, q);
+    b = csub(p, q);
+  } else if constexpr (CJ) {  // conj(a -+ i b) = conj a +- i conj b
+    a = cadd_i(p, q);
+    b = csub_i(p, q);
+  } else {
+    a = csub_i(p, q);
+    b = cadd_i(p, q);
+  }
+}
+
+// acc + g u and acc - g u, conjugated if CJ; NEGI: -i u for u
+template <bool NEGI, bool CJ>
+__device__ __forceinline__ void bf_scaled(c32 &a, c32 &b, c32 u, float g) {
+  BFP_NO_CONTRACT
+  const float ux = NEGI ? u.y : u.x, uy = NEGI ? -u.x : u.y;
+  const c32 p = c32{__builtin_fmaf(ux, g, a.x), CJ ? __builtin_fmaf(-uy, g, -a.y) : __builtin_fmaf(uy, g, a.y)};
+  const c32 q = c32{__builtin_fmaf(-ux, g, a.x), CJ ? __builtin_fmaf(uy, g, -a.y) : __builtin_fmaf(-uy, g, a.y)};
+  a = p;
+  b = q;
+}
+template <bool NEGI, bool CJ>
+__device__ __forceinline__ void bf_scaled(h2 &a, h2 &b, h2 u, f16 g) {
+  BFP_NO_CONTRACT
+  const h2 r = NEGI ? h2{u.y, -u.x} : u, gg = h2{g, g};
+  const h2 c = CJ ? cconj(a) : a, v = CJ ? cconj(r) : r;
+  a = __builtin_elementwise_fma(v, gg, c);
+  b = __builtin_elementwise_fma(-v, gg, c);
+}
+
+template <bool COS>
+__device__ __forceinline__ c32 bf_turn(c32 b, float t) {
+  BFP_NO_CONTRACT
+  if constexpr (COS) return c32{__builtin_fmaf(-b.y, t, b.x), __builtin_fmaf(b.x, t, b.y)};
+  else return c32{__builtin_fmaf(b.x, t, -b.y), __builtin_fmaf(b.y, t, b.x)};
+}
+template <bool COS>
+__device__ __forceinline__ h2 bf_turn(h2 b, f16 t) {
+  BFP_NO_CONTRACT
+  if constexpr (COS) return __builtin_elementwise_fma(h2{-b.y, b.x}, h2{t, t}, b);
+  else return __builtin_elementwise_fma(b, h2{t, t}, h2{-b.y, b.x});
+}
+template <bool COS, bool NEGI, bool CJ, class C, class W>
+__device__ __forceinline__ void bf_tan(C &a, C &b, W w) {  // w = (g, t)
+  bf_scaled<NEGI, CJ>(a, b, bf_turn<COS>(b, w.y), w.x);
+}
+
+template <bool NEGI, bool CJ>
+__device__ __forceinline__ void bf_fma(c32 &a, c32 &b, c32 w) {
+  BFP_NO_CONTRACT
+  const float wx = NEGI ? w.y : w.x, wy = NEGI ? -w.x : w.y;
+  const float px = __builtin_fmaf(wx, b.x, __builtin_fmaf(-wy, b.y, a.x));
+  const float qx = __builtin_fmaf(-wx, b.x, __builtin_fmaf(wy, b.y, a.x));
+  const float sg = CJ ? -1.0f : 1.0f;  // folds into the operands' signs
+  const float py = __builtin_fmaf(sg * wx, b.y, __builtin_fmaf(sg * wy, b.x, sg * a.y));
+  const float qy = __builtin_fmaf(-(sg * wx), b.y, __builtin_fmaf(-(sg * wy), b.x, sg * a.y));
+  a = c32{px, py};
+  b = c32{qx, qy};
+}
+template <bool NEGI, bool CJ>
+__device__ __forceinline__ void bf_fma(h2 &a, h2 &b, h2 w) {
+  BFP_NO_CONTRACT
+  const h2 r = NEGI ? h2{b.y, -b.x} : b;
+  const h2 m = CJ ? h2{-r.y, -r.x} : h2{-r.y, r.x};  // i r, conjugated if CJ
+  const h2 n = CJ ? cconj(r) : r, c = CJ ? cconj(a) : a;
+  const h2 wx = h2{w.x, w.x}, wy = h2{w.y, w.y};
+  a = __builtin_elementwise_fma(n, wx, __builtin_elementwise_fma(m, wy, c));
+  b = __builtin_elementwise_fma(-n, wx, __builtin_elementwise_fma(-m, wy, c));
+}
+
+template <bool NEGI, bool CJ, class C, class W>
+__device__ __forceinline__ void bf_twice(C &a, C &b, W w) {
+  BFP_NO_CONTRACT
+  const C c = CJ ? cconj(a) : a;
+  C p = a, q = b;
+  bf_fma<NEGI, CJ>(p, q, w);  // the difference of this form is not used
+  a = p;
+  if constexpr (sizeof(C) == 8) b = C{__builtin_fmaf(2.0f, c.x, -p.x), __builtin_fmaf(2.0f, c.y, -p.y)};
+  else b = __builtin_elementwise_fma(c, C{(f16)2.0f, (f16)2.0f}, -p);
+}
+
+// ------------------------------------------------------------ DFTs ------
+// Length-R DFT of x_r omega^r, omega = W_{NS R}^m the twiddle base of a
+// Stockham pass, by decimation in time: with E and O the DFT_{R/2} of the
+// even and odd elements on base omega^2,
+//   X_k = E_k + (omega W_R^k) O_k,  X_{k + R/2} = E_k - (omega W_R^k) O_k,
+// so the twiddles are merged into the butterflies, and since
+// omega W_R^{k + R/4} = -i omega W_R^k a level takes R/4 values: R/2 for all
+// levels (level R first, then R/2 ...; level 2 one), where separate products
+// take R - 1.  The angle of omega W_R^k lies in (-2 pi (k + 1) / R,
+// -2 pi k / R]: from R = 8 on each k < R/4 is on one side of -pi/4 for every
+// m, and the tangent form is chosen at compile time.  At R = 4 the angle of
+// omega spans (-pi/2, 0] and at R = 2 (-pi, 0]: those take (re, im), level 4
+// as bf_fma (bf_twice with TWICE4) and level 2 as bf_twice.  A radix-16 pass
+// takes 208 FP32 operations on 16 values (192 with TWICE4; 220 with 15
+// products and a 4 x 4 DFT16) or 104 packed FP16 ones (110), and half the
+// table reads.  Error against FP64 on N(0, 1) input relative to the products,
+// 4096 points: 1.00 in FP32 and FP16 (1.02 with TWICE4, which serves the mode
+// whose error is the FP16 rounding of its exchanges); 0.99 to 1.04 at other
+// sizes and radices.
+template <int R>
+constexpr int tw_level() { return R >= 4 ? R / 4 : 1; }  // those of level R
+
+template <int R, bool CJ, bool TWICE4, class C, class W>
+__device__ __forceinline__ void dft_tw(C (&x)[R], const W *w) {
+  if constexpr (R == 2) {
+    bf_twice<false, CJ>(x[0], x[1], w[0]);
+  } else {
+    C e[R / 2], o[R / 2];
+#pragma unroll
+    for (int k = 0; k < R / 2; ++k) {
+      e[k] = x[2 * k];
+      o[k] = x[2 * k + 1];
+    }
+    dft_tw<R / 2, false, TWICE4>(e, w + tw_level<R>());
+    dft_tw<R / 2, false, TWICE4>(o, w + tw_level<R>());
+#pragma unroll
+    for (int k = 0; k < R / 4; ++k) {
+      const int k2 = k + R / 4;
+      if constexpr (R == 4 && TWICE4) {
+        bf_twice<false, CJ>(e[k], o[k], w[k]);
+        bf_twice<true, CJ>(e[k2], o[k2], w[k]);
+      } else if constexpr (R == 4) {
+        bf_fma<false, CJ>(e[k], o[k], w[k]);
+        bf_fma<true, CJ>(e[k2], o[k2], w[k]);
+      } else if (k < R / 8) {
+        bf_tan<true, false, CJ>(e[k], o[k], w[k]);
+        bf_tan<true, true, CJ>(e[k2], o[k2], w[k]);
+      } else {
+        bf_tan<false, false, CJ>(e[k], o[k], w[k]);
+        bf_tan<false, true, CJ>(e[k2], o[k2], w[k]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < R / 2; ++k) {
+      x[k] = e[k];
+      x[k + R / 2] = o[k];
+    }
+  }
+}
+
+// tan and cos of pi e / 16 (e = 1, 2, 3, 4), to 20 significant digits
+constexpr float kTan16[5] = {0.0f, 0.19891236737965800691f, 0.41421356237309504880f,
+                             0.66817863791929891999f, 1.0f};
+constexpr float kCos16[5] = {1.0f, 0.98078528040323044913f, 0.92387953251128675613f,
+                             0.83146961230254523708f, 0.70710678118654752440f};
+__device__ __forceinline__ c32 tan_pair(c32, float g, float t) { return c32{g, t}; }
+__device__ __forceinline__ h2 tan_pair(h2, float g, float t) { return h2{(f16)g, (f16)t}; }
+
+// How the first level of a first pass takes its pairs (x_r, x_{r + R/2}):
+//   LeafPlain   a + b, a - b;
+//   LeafScaled  a + s b, a - s b as FMAs, a scaled already: the block shift
+//               s = 2^-K of an inverse then costs FP32 pairs half its
+//               multiplications, with the same bits (s b is exact).  With an
+//               s that the compiler cannot see to be 1, FP16 operands reach
+//               the FMA without a conversion (v_fma_mix_f32).
+struct LeafPlain {};
+struct LeafScaled {
+  float s;
+};
+__device__ __forceinline__ LeafScaled leaf_one() {
+  float s = 1.0f;
+  asm("" : "+s"(s));
+  return LeafScaled{s};
+}
+template <class C, int K>
+using FoldLeaf = std::conditional_t<std::is_same<C, c32>::value && (K > 0), LeafScaled, LeafPlain>;
+template <class C, int K>
+__device__ __forceinline__ FoldLeaf<C, K> fold_leaf() {
+  if constexpr (std::is_same<C, c32>::value && K > 0) return LeafScaled{1.0f / (1 << K)};
+  else return LeafPlain{};
+}
+// element e of E on its way into such a first pass: conj(z) 2^-K, or z 2^-K
+// (CONJ = false), with the factor left to the leaf in the second half
+template <int K, int E, bool CONJ = true, class C>
+__device__ __forceinline__ C fold_in(C z, int e) {
+  if (std::is_same<C, c32>::value && K > 0 && e >= E / 2) return CONJ ? conj_store(z) : z;
+  return CONJ ? conj_pow2<K>(z) : pow2<K>(z);
+}
+
+template <class C>
+__device__ __forceinline__ void bf_leaf(C &a, C &b, LeafPlain) {
+  bf_one<false, false>(a, b);
+}
+__device__ __forceinline__ void bf_leaf(c32 &a, c32 &b, LeafScaled l) {
+  BFP_NO_CONTRACT
+  const c32 p = c32{__builtin_fmaf(b.x, l.s, a.x), __builtin_fmaf(b.y, l.s, a.y)};
+  b = c32{__builtin_fmaf(-b.x, l.s, a.x), __builtin_fmaf(-b.y, l.s, a.y)};
+  a = p;
+}
+
+// The same with omega = 1 (the first pass, and transforms in one pass):
+// W_R^k = cos a - i sin a, a = 2 pi k / R, are constants.
+template <int R, bool CJ = false, class C, class Leaf = LeafPlain>
+__device__ __forceinline__ void dft(C (&x)[R], Leaf leaf = Leaf{}) {
+  static_assert(R == 2 || R == 4 || R == 8 || R == 16 || R == 32, "radix");
+  if constexpr (R == 2) {
+    if constexpr (CJ) bf_one<false, true>(x[0], x[1]);  // a last pass of radix 2
+    else bf_leaf(x[0], x[1], leaf);
+  } else {
+    C e[R / 2], o[R / 2];
+#pragma unroll
+    for (int k = 0; k < R / 2; ++k) {
+      e[k] = x[2 * k];
+      o[k] = x[2 * k + 1];
+    }
+    dft<R / 2>(e, leaf);
+    dft<R / 2>(o, leaf);
+    bf_one<false, CJ>(e[0], o[0]);
+    bf_one<true, CJ>(e[R / 4], o[R / 4]);
+#pragma unroll
+    for (int k = 1; k < R / 4; ++k) {
+      const int k2 = k + R / 4, s = 32 / R * k;  // a = pi s / 16
+      if (s <= 4) {  // cos a (1 - i tan a)
+        const C w = tan_pair(C{}, kCos16[s], -kTan16[s]);
+        bf_tan<true, false, CJ>(e[k], o[k], w);
+        bf_tan<true, true, CJ>(e[k2], o[k2], w);
+      } else {       // -sin a (-cot a + i), with sin a = cos(pi/2 - a)
+        const C w = tan_pair(C{}, -kCos16[8 - s], -kTan16[8 - s]);
+        bf_tan<false, false, CJ>(e[k], o[k], w);
+        bf_tan<false, true, CJ>(e[k2], o[k2], w);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < R / 2; ++k) {
+      x[k] = e[k];
+      x[k + R / 2] = o[k];
+    }
+  }
+}
+
+// ---------------------------------------------- DFTs after products ------
+// Packed FP16 DFTs by radix-4 steps, for the passes whose twiddles are
+// products ahead of the DFT (ModeFP16Products).  CJ returns the conjugated
+// outputs: the last combining step takes conjugated operands (conj(x + y) =
+// conj x + conj y, conj(-i y) = i conj y), source negations of the packed
+// adds.
 #define BFP_C8 0.70710678118654752440f
 #define BFP_C16 0.92387953251128675613f
 #define BFP_S16 0.38268343236508977173f
 
-// a * W_R^e, W_R = exp(-2 pi i / R), e a compile-time constant
-template <int R, int E, class C>
-__device__ __forceinline__ C mulw(C a) {
-  constexpr int e = ((E % R) + R) % R;
-  if constexpr (e == 0) {
-    return a;
-  } else if constexpr (4 * e == R) {
-    return mul_mi(a);
-  } else if constexpr (2 * e == R) {
-    return cneg(a);
-  } else if constexpr (4 * e == 3 * R) {
-    return mul_pi(a);
-  } else if constexpr (8 * e == R) {
-    return mul_1mi(a, BFP_C8);       // e^{-i pi/4}
-  } else if constexpr (8 * e == 3 * R) {
-    return mul_m1mi(a, BFP_C8);      // e^{-3i pi/4}
-  } else if constexpr (8 * e == 5 * R) {
-    return mul_m1pi(a, BFP_C8);      // e^{-5i pi/4}
-  } else if constexpr (8 * e == 7 * R) {
-    return mul_1pi(a, BFP_C8);       // e^{-7i pi/4}
-  } else {
-    static_assert(R == 16, "generic constant twiddles only for radix 16");
-    // e odd: angle = 2 pi e / 16 = e pi / 8
-    constexpr int q = e;  // 1,3,5,7,9,11,13,15
-    constexpr float c = (q == 1 || q == 15) ? BFP_C16
-                      : (q == 3 || q == 13) ? BFP_S16
-                      : (q == 5 || q == 11) ? -BFP_S16
-                                            : -BFP_C16;  // 7, 9
-    constexpr float s = (q == 1 || q == 7) ? -BFP_S16
-                      : (q == 3 || q == 5) ? -BFP_C16
-                      : (q == 9 || q == 15) ? BFP_S16
-                                            : BFP_C16;   // 11, 13
-    return cmulk(a, c, s);
+__device__ __forceinline__ h2 rot_mi(h2 a) { return h2{a.y, -a.x}; }  // x (-i)
+__device__ __forceinline__ h2 rot_pi(h2 a) { return h2{-a.y, a.x}; }  // x (+i)
+
+// a * W_R^e, W_R = exp(-2 pi i / R), e a compile-time constant below R / 2 + 2
+template <int R, int e>
+__device__ __forceinline__ h2 mulw(h2 a) {
+  const h2 k8 = h2{(f16)BFP_C8, (f16)BFP_C8};
+  if constexpr (e == 0) return a;
+  else if constexpr (4 * e == R) return rot_mi(a);
+  else if constexpr (8 * e == R) return (a + rot_mi(a)) * k8;      // e^{-i pi/4}
+  else if constexpr (8 * e == 3 * R) return (rot_mi(a) - a) * k8;  // e^{-3i pi/4}
+  else {
+    static_assert(R == 16 && (e == 1 || e == 3 || e == 9), "odd powers of W_16 of a 4 x 4 DFT16");
+    return cmul(a, h2{(f16)(e == 1 ? BFP_C16 : e == 3 ? BFP_S16 : -BFP_C16),
+                      (f16)(e == 1 ? -BFP_S16 : e == 3 ? -BFP_C16 : BFP_S16)});
   }
 }
 
-// ------------------------------------------------------------ DFTs ------
-// In-place length-R DFT (forward sign), natural order in and out.
-// CJ = true returns the conjugated outputs: the last combining step takes
-// conjugated operands (conj(x + y) = conj x + conj y, conj(-i y) = i conj y),
-// which the packed adds apply as source negations, so the conjugate at the
-// end of an inverse transform costs no instruction.
-template <bool CJ = false, class C>
-__device__ __forceinline__ void dft2(C &a, C &b) {
-  C t = CJ ? cconj(a) : a;
-  C u = CJ ? cconj(b) : b;
-  a = cadd(t, u);
-  b = csub(t, u);
-}
-
-template <bool CJ = false, class C>
-__device__ __forceinline__ void dft4(C &a, C &b, C &c, C &d) {
-  C s0 = cadd(a, c), s1 = csub(a, c), s2 = cadd(b, d), s3 = csub(b, d);
+template <bool CJ = false>
+__device__ __forceinline__ void dft4(h2 &a, h2 &b, h2 &c, h2 &d) {
+  h2 s0 = cadd(a, c), s1 = csub(a, c), s2 = cadd(b, d), s3 = csub(b, d);
   if constexpr (CJ) {
     s0 = cconj(s0);
     s1 = cconj(s1);
@@ -218,30 +400,34 @@ __device__ __forceinline__ void dft4(C &a, C &b, C &c, C &d) {
   }
 }
 
-template <int R, bool CJ = false, class C>
-__device__ __forceinline__ void dft(C *v) {
+// In place, natural order in and out.
+template <int R, bool CJ>
+__device__ __forceinline__ void dft_steps(h2 (&v)[R]) {
   if constexpr (R == 2) {
-    dft2<CJ>(v[0], v[1]);
+    static_assert(!CJ, "conjugates fold into a radix-4 step only");
+    const h2 t = v[0], u = v[1];
+    v[0] = cadd(t, u);
+    v[1] = csub(t, u);
   } else if constexpr (R == 4) {
     dft4<CJ>(v[0], v[1], v[2], v[3]);
   } else if constexpr (R == 8) {
     // n = n2 + 2 n1 (n2 < 2, n1 < 4), k = k1 + 4 k2
+    static_assert(!CJ, "conjugates fold into a radix-4 step only");
     dft4(v[0], v[2], v[4], v[6]);  // n2 = 0 -> slots 0,2,4,6 hold k1 = 0..3
     dft4(v[1], v[3], v[5], v[7]);  // n2 = 1
     v[3] = mulw<8, 1>(v[3]);
     v[5] = mulw<8, 2>(v[5]);
     v[7] = mulw<8, 3>(v[7]);
-    C y[8];
+    h2 y[8];
 #pragma unroll
     for (int k1 = 0; k1 < 4; ++k1) {
-      const C p = CJ ? cconj(v[2 * k1]) : v[2 * k1];
-      const C q = CJ ? cconj(v[2 * k1 + 1]) : v[2 * k1 + 1];
-      y[k1] = cadd(p, q);
-      y[k1 + 4] = csub(p, q);
+      y[k1] = cadd(v[2 * k1], v[2 * k1 + 1]);
+      y[k1 + 4] = csub(v[2 * k1], v[2 * k1 + 1]);
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = y[i];
-  } else if constexpr (R == 16) {
+  } else {
+    static_assert(R == 16, "radix");
     // n = n2 + 4 n1, k = k1 + 4 k2: DFT4 over n1, twiddle W16^{n2 k1},
     // DFT4 over n2.
 #pragma unroll
@@ -259,15 +445,13 @@ __device__ __forceinline__ void dft(C *v) {
 #pragma unroll
     for (int k1 = 0; k1 < 4; ++k1) dft4<CJ>(v[4 * k1], v[4 * k1 + 1], v[4 * k1 + 2], v[4 * k1 + 3]);
     // slot k2 + 4 k1 holds X[k1 + 4 k2]: transpose the 4x4 slot grid
-    C y[16];
+    h2 y[16];
 #pragma unroll
     for (int k1 = 0; k1 < 4; ++k1)
 #pragma unroll
       for (int k2 = 0; k2 < 4; ++k2) y[k1 + 4 * k2] = v[k2 + 4 * k1];
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = y[i];
-  } else {
-    static_assert(R == 2 || R == 4 || R == 8 || R == 16, "radix");
   }
 }
 
@@ -372,71 +556,111 @@ __device__ __forceinline__ void st_stream_g(global_ptr<T> p, T v) {
 // Each mode defines:
 //   Store: HBM element; Lds: on-chip element between passes;
 //   Comp: register arithmetic type; Tw: twiddle table element;
-//   Filt: filter element.
+//   Filt: filter element;
+//   kMerged: twiddles merged into the butterflies (dft_tw, with kTwice4 as
+//   its TWICE4), or a product per value (twiddle) ahead of dft;
+//   first_leaf(): how a first pass takes values as decoded
 // and the conversions/multiplies the engine needs.
 
 struct ModeFP32 {
   typedef c32 Store; typedef c32 Lds; typedef c32 Comp; typedef c32 Tw; typedef c32 Filt;
+  static constexpr bool kMerged = true, kTwice4 = false;
+  static __device__ __forceinline__ LeafPlain first_leaf() { return LeafPlain{}; }
   static __device__ __forceinline__ Comp decode(Store s) { return s; }
   static __device__ __forceinline__ Store encode(Comp v) { return v; }
   static __device__ __forceinline__ Comp load(const Store *p, unsigned i) { return ld_stream(p + i); }
   static __device__ __forceinline__ void store(Store *p, unsigned i, Comp v) { st_stream(p + i, v); }
   static __device__ __forceinline__ Lds to_lds(Comp v) { return v; }
   static __device__ __forceinline__ Comp from_lds(Lds v) { return v; }
-  static __device__ __forceinline__ Comp twiddle(Lds v, Tw w) { return cmul(v, w); }
   static __device__ __forceinline__ Comp fmul(Comp v, Filt h) { return cmul(v, h); }
   static __device__ __forceinline__ Comp round_store(Comp v) { return v; }
 };
 
 struct ModeFP16 {  // pure packed FP16
   typedef h2 Store; typedef h2 Lds; typedef h2 Comp; typedef h2 Tw; typedef h2 Filt;
+  static constexpr bool kMerged = true, kTwice4 = false;
+  static __device__ __forceinline__ LeafPlain first_leaf() { return LeafPlain{}; }
   static __device__ __forceinline__ Comp decode(Store s) { return s; }
   static __device__ __forceinline__ Store encode(Comp v) { return v; }
   static __device__ __forceinline__ Comp load(const Store *p, unsigned i) { return ld_stream(p + i); }
   static __device__ __forceinline__ void store(Store *p, unsigned i, Comp v) { st_stream(p + i, v); }
   static __device__ __forceinline__ Lds to_lds(Comp v) { return v; }
   static __device__ __forceinline__ Comp from_lds(Lds v) { return v; }
-  static __device__ __forceinline__ Comp twiddle(Lds v, Tw w) { return cmul(v, w); }
   static __device__ __forceinline__ Comp fmul(Comp v, Filt h) { return cmul(v, h); }
   static __device__ __forceinline__ Comp round_store(Comp v) { return v; }
 };
 
+// Pure FP16 with twiddles as products ahead of radix-4 steps: the sizes up to
+// 4096 points, whose fused compressions hold the twiddles in registers.  The
+// merged butterflies save 6% of the arithmetic there and no time (16.1 us
+// either way for the 2048 x 4096 compression, 31 us for 4096 x 4096); above,
+// where every pass reads the table, they take 103 instead of 110 us for a
+// forward and an inverse of 2047 x 16384.
+struct ModeFP16Products : ModeFP16 {
+  static constexpr bool kMerged = false;
+  static __device__ __forceinline__ Comp twiddle(Lds v, Tw w) { return cmul(v, w); }
+};
+// the arithmetic of a mode at a size (merged_twiddles() on the host)
+template <class M, int LOG2N>
+using SizeMode = std::conditional_t<std::is_same<M, ModeFP16>::value && LOG2N <= 12, ModeFP16Products, M>;
+
 __device__ __forceinline__ c32 h2_to_c32(h2 v) { return c32{(float)v.x, (float)v.y}; }
 
-// Natural logarithm of a positive FP32 value from the hardware base-2
-// logarithm (v_log_f32, about 1 ulp) and one multiply, instead of the
-// library's correctly-scaled sequence (about 11 instructions more).  The
-// hardware instruction does not take denormal inputs, so arguments below the
-// smallest normal number are raised to it: for an image power p that small
+// Base-2 logarithm of a positive FP32 value: the hardware's (v_log_f32,
+// about 1 ulp) instead of the library's correctly-scaled sequence (about 11
+// instructions more); sums and factors take their ln 2 once, not per value.
+// The hardware instruction does not take denormal inputs, so arguments below
+// the smallest normal number are raised to it: for an image power p that small
 // the terms p ln p and p (ln p + c) are below 1e-36.
-__device__ __forceinline__ float ln_pos(float a) {
-  return __builtin_amdgcn_logf(fmaxf(a, 1.17549435e-38f)) * 0.693147180559945309f;
+constexpr double kLn2 = 0.693147180559945309417;
+__device__ __forceinline__ float log2_pos(float a) {
+  return __builtin_amdgcn_logf(fmaxf(a, 1.17549435e-38f));
 }
-__device__ __forceinline__ h2 c32_to_h2(c32 v) { return h2{(f16)v.x, (f16)v.y}; }
+// Rounded as a pair (v_cvt_pk_f16_f32).  Two scalar conversions may be folded
+// into the FMAs that made v.x and v.y (v_fma_mixlo/mixhi_f16), in one kernel
+// and not in another, and would then round once where the pair rounds twice.
+__device__ __forceinline__ h2 c32_to_h2(c32 v) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  return __builtin_convertvector((f32x2{v.x, v.y}), h2);
+}
 
 struct ModeF16StoreF32 {
   typedef h2 Store; typedef h2 Lds; typedef c32 Comp; typedef c32 Tw; typedef h2 Filt;
+  static constexpr bool kMerged = true, kTwice4 = true;
+  static __device__ __forceinline__ LeafScaled first_leaf() { return leaf_one(); }
   static __device__ __forceinline__ Comp decode(Store s) { return h2_to_c32(s); }
   static __device__ __forceinline__ Store encode(Comp v) { return c32_to_h2(v); }
   static __device__ __forceinline__ Comp load(const Store *p, unsigned i) { return h2_to_c32(ld_stream(p + i)); }
   static __device__ __forceinline__ void store(Store *p, unsigned i, Comp v) { st_stream(p + i, c32_to_h2(v)); }
   static __device__ __forceinline__ Lds to_lds(Comp v) { return c32_to_h2(v); }
   static __device__ __forceinline__ Comp from_lds(Lds v) { return h2_to_c32(v); }
-  static __device__ __forceinline__ Comp twiddle(Lds v, Tw w) { return cmul(h2_to_c32(v), w); }
-  static __device__ __forceinline__ Comp fmul(Comp v, Filt h) { return cmul(v, h2_to_c32(h)); }
+  // cmul(v, h) with its plain products as FMAs on 0, which take h as stored
+  // (v_fma_mix_f32): a product needs a conversion
+  static __device__ __forceinline__ Comp fmul(Comp v, Filt h) {
+    BFP_NO_CONTRACT
+    const c32 f = h2_to_c32(h);
+    return c32{__builtin_fmaf(v.x, f.x, __builtin_fmaf(-v.y, f.y, 0.0f)),
+               __builtin_fmaf(v.x, f.y, __builtin_fmaf(v.y, f.x, 0.0f))};
+  }
   static __device__ __forceinline__ Comp round_store(Comp v) { return h2_to_c32(c32_to_h2(v)); }
 };
 
-// FP16 operands, FP32 accumulation: (a.x, a.y) . (b.x, -b.y) and
-// (a.x, a.y) . (b.y, b.x) with v_dot2_f32_f16.
+// FP16 operands, FP32 accumulation: a b as (a.x, a.y) . (b.x, -b.y) and
+// (a.x, a.y) . (b.y, b.x) with v_dot2_f32_f16, for which the compiler folds no
+// operand selects: the second operands are one flip of the high sign and one
+// rotation (a table of both operands doubles its reads, which cost more than
+// the two instructions: 37 against 27 us for the 2048 x 4096 compression).
 __device__ __forceinline__ c32 cmul_dot2(h2 a, h2 b) {
-  float re = __builtin_amdgcn_fdot2(a, h2{b.x, -b.y}, 0.0f, false);
-  float im = __builtin_amdgcn_fdot2(a, h2{b.y, b.x}, 0.0f, false);
-  return c32{re, im};
+  const uint32_t u = __builtin_bit_cast(uint32_t, b);
+  const h2 re = __builtin_bit_cast(h2, u ^ 0x80000000u);
+  const h2 im = __builtin_bit_cast(h2, __builtin_amdgcn_alignbit(u, u, 16));
+  return c32{__builtin_amdgcn_fdot2(a, re, 0.0f, false), __builtin_amdgcn_fdot2(a, im, 0.0f, false)};
 }
 
 struct ModeF16MulF32Acc {
   typedef h2 Store; typedef h2 Lds; typedef c32 Comp; typedef h2 Tw; typedef h2 Filt;
+  static constexpr bool kMerged = false, kTwice4 = false;
+  static __device__ __forceinline__ LeafScaled first_leaf() { return leaf_one(); }
   static __device__ __forceinline__ Comp decode(Store s) { return h2_to_c32(s); }
   static __device__ __forceinline__ Store encode(Comp v) { return c32_to_h2(v); }
   static __device__ __forceinline__ Comp load(const Store *p, unsigned i) { return h2_to_c32(ld_stream(p + i)); }
@@ -451,6 +675,8 @@ struct ModeF16MulF32Acc {
 template <int MANT, int BIAS>
 struct ModeFP8 {
   typedef fp8x2 Store; typedef c32 Lds; typedef c32 Comp; typedef c32 Tw; typedef c32 Filt;
+  static constexpr bool kMerged = true, kTwice4 = false;
+  static __device__ __forceinline__ LeafPlain first_leaf() { return LeafPlain{}; }
   typedef Fp8Codec<MANT> Codec;
   static __device__ __forceinline__ Comp decode(Store b) {
     return Codec::decode2(__builtin_bit_cast(uint16_t, b));
@@ -462,7 +688,6 @@ struct ModeFP8 {
   static __device__ __forceinline__ void store(Store *p, unsigned i, Comp v) { st_stream(p + i, encode(v)); }
   static __device__ __forceinline__ Lds to_lds(Comp v) { return v; }
   static __device__ __forceinline__ Comp from_lds(Lds v) { return v; }
-  static __device__ __forceinline__ Comp twiddle(Lds v, Tw w) { return cmul(v, w); }
   static __device__ __forceinline__ Comp fmul(Comp v, Filt h) { return cmul(v, h); }
   static __device__ __forceinline__ Comp round_store(Comp v) { return decode(encode(v)); }
 };

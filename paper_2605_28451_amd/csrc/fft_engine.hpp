@@ -15,9 +15,14 @@
 // scattered Stockham writes and the reads free of bank conflicts.
 //
 // Twiddles come from a per-plan table in HBM (L2/L1-resident after the first
-// wavefronts): pass p owns NS_p x R_p entries W_{NS R}^{m r}, m < NS, r < R,
-// built on the host in FP64 and rounded once to the mode's twiddle type.
+// wavefronts), built on the host in FP64 and rounded once to the mode's
+// twiddle type: pass p owns a row for each m < NS, the R / 2 entries that the
+// merged butterflies of dft_tw take on base W_{NS R}^m, or, in the
+// FP16-multiply mode (products of FP16 operands ahead of the DFT), the R
+// entries W_{NS R}^{m r}.
 #pragma once
+
+#include <type_traits>
 
 #include "fft_device.hpp"
 
@@ -116,13 +121,15 @@ struct Geometry {
     for (int q = 0; q < p; ++q) ns *= radix(q);
     return ns;
   }
-  // offset of pass p's twiddle block in the plan table (passes with NS > 1)
-  static constexpr int tw_offset(int p) {
+  // entries of one twiddle row of pass p, and the offset of its block in the
+  // plan table (passes with NS > 1)
+  static constexpr int tw_row(int p, bool merged) { return merged ? radix(p) / 2 : radix(p); }
+  static constexpr int tw_offset(int p, bool merged) {
     int off = 0;
-    for (int q = 1; q < p; ++q) off += span(q) * radix(q);
+    for (int q = 1; q < p; ++q) off += span(q) * tw_row(q, merged);
     return off;
   }
-  static constexpr int tw_entries() { return tw_offset(S::P); }
+  static constexpr int tw_entries(bool merged) { return tw_offset(S::P, merged); }
 };
 
 // Offset of element d in a layout, relative to a base whose position is a
@@ -207,42 +214,85 @@ struct Engine {
   typedef typename M::Tw Tw;
   static constexpr int E = G::E;
   static constexpr int T = G::T;
-  // Conjugated outputs (CJ) are folded into the last pass when it ends in a
-  // DFT4 stage (radix 4 or 16), whose outputs are sums of sums: conj of a
-  // sum is then exactly the sum of conjugates.  A radix-2 or radix-8 last
-  // pass adds products, which the compiler may contract into FMAs
-  // differently once conjugates sit in between, so there the conjugate
-  // follows the transform and every kernel rounds alike.
+  // Conjugated outputs (CJ) are folded into the last pass as signs, except
+  // after a radix-2 or radix-8 step form (dft_steps), whose last additions the
+  // compiler may contract with products differently once signs sit in between:
+  // there the conjugate follows the transform and every kernel rounds alike.
+  static constexpr bool kSteps = !M::kMerged && std::is_same<Comp, h2>::value;
   static constexpr int kLastRadix = G::radix(G::S::P - 1);
-  static constexpr bool kFoldConj = kLastRadix == 4 || kLastRadix == 16;
+  static constexpr bool kFoldConj = !kSteps || kLastRadix == 4 || kLastRadix == 16;
+  // Twiddle rows of a pass held by a thread: one per butterfly.
+  static constexpr int TWN = M::kMerged ? E / 2 : E;
 
   // Twiddle rows of pass PASS for this thread: butterfly b uses row
-  // (t + T b) mod NS, entries r = 0..R-1, kept at w[b R + r].
+  // (t + T b) mod NS.
   template <int PASS>
-  static __device__ __forceinline__ void load_tw(const Tw *__restrict__ tw, int t, Tw (&w)[E]) {
+  static __device__ __forceinline__ void load_tw(const Tw *__restrict__ tw, int t, Tw (&w)[TWN]) {
     if constexpr (PASS > 0 && PASS < G::S::P) {
-      constexpr int R = G::radix(PASS);
       constexpr int NS = G::span(PASS);
-      constexpr int B = E / R;
-      const Tw *twp = tw + G::tw_offset(PASS);
+      constexpr int B = E / G::radix(PASS), Q = G::tw_row(PASS, M::kMerged);
+      const Tw *twp = tw + G::tw_offset(PASS, M::kMerged);
 #pragma unroll
       for (int b = 0; b < B; ++b) {
-        const Tw *row = twp + ((t + T * b) & (NS - 1)) * R;
+        const Tw *row = twp + ((t + T * b) & (NS - 1)) * Q;
 #pragma unroll
-        for (int r = 0; r < R; ++r) w[b * R + r] = row[r];
+        for (int r = 0; r < Q; ++r) w[b * Q + r] = row[r];
       }
+    }
+  }
+
+  // v[e] of a pass after the first from the values read out of LDS: element
+  // b + B r is input r of butterfly b.
+  template <int PASS>
+  static __device__ __forceinline__ void gather(Comp (&v)[E], const Lds (&raw)[E], const Tw (&w)[TWN]) {
+    constexpr int R = G::radix(PASS), B = E / R;
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      v[b] = M::from_lds(raw[b]);
+#pragma unroll
+      for (int r = 1; r < R; ++r) {
+        if constexpr (M::kMerged) v[b + B * r] = M::from_lds(raw[b + B * r]);
+        else v[b + B * r] = M::twiddle(raw[b + B * r], w[b * R + r]);
+      }
+    }
+  }
+
+  // The E / R butterflies of a pass (conjugated outputs: CJ, last pass).
+  template <int PASS, bool CJ, class Leaf>
+  static __device__ __forceinline__ void butterflies(Comp (&v)[E], const Tw (&w)[TWN], Leaf leaf) {
+    constexpr int R = G::radix(PASS), B = E / R;
+    constexpr bool cj = CJ && PASS == G::S::P - 1 && kFoldConj;
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      Comp u[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) u[r] = v[b + B * r];
+      if constexpr (kSteps) dft_steps<R, cj>(u);
+      else if constexpr (PASS > 0 && M::kMerged) dft_tw<R, cj, M::kTwice4>(u, w + b * (R / 2));
+      else if constexpr (PASS > 0) dft<R, cj>(u);
+      else dft<R, cj>(u, leaf);
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[b + B * r] = u[r];
+    }
+  }
+
+  template <bool CJ>
+  static __device__ __forceinline__ void conj_unfolded(Comp (&v)[E]) {
+    if constexpr (CJ && !kFoldConj) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[e] = conj_store(v[e]);
     }
   }
 
   // One Stockham pass.  On entry v[e] holds this thread's inputs (pass 0)
   // or nothing (later passes, which read LDS), and w this pass's twiddle
-  // rows; the next pass's rows are loaded into w as soon as this pass has
-  // consumed its own, so their latency overlaps the butterflies and the LDS
-  // exchange.  On exit v[e] holds the outputs (last pass) or the outputs
-  // have been written to LDS.
-  template <int PASS, bool PREFETCH = true, bool CJ = false>
+  // rows; the next pass's rows are loaded into wn once this pass's inputs are
+  // read, so their latency overlaps the butterflies and the LDS exchange.
+  // On exit v[e] holds the outputs (last pass) or the outputs have been
+  // written to LDS.
+  template <int PASS, bool CJ, class Leaf>
   static __device__ __forceinline__ void pass(Comp (&v)[E], Lds *lds, const Tw *__restrict__ tw,
-                                              int t, Tw (&w)[E]) {
+                                              int t, const Tw (&w)[TWN], Tw (&wn)[TWN], Leaf leaf) {
     constexpr int R = G::radix(PASS);
     constexpr int NS = G::span(PASS);
     constexpr int B = E / R;
@@ -253,23 +303,10 @@ struct Engine {
       const int tp = In::at(t);
 #pragma unroll
       for (int e = 0; e < E; ++e) raw[e] = lds[lds_slot<In, T>(tp, e)];
-#pragma unroll
-      for (int b = 0; b < B; ++b) {
-        v[b] = M::from_lds(raw[b]);
-#pragma unroll
-        for (int r = 1; r < R; ++r) v[b + B * r] = M::twiddle(raw[b + B * r], w[b * R + r]);
-      }
+      gather<PASS>(v, raw, w);
     }
-    if constexpr (PREFETCH) load_tw<PASS + 1>(tw, t, w);
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-      Comp u[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) u[r] = v[b + B * r];
-      dft<R, CJ && LAST && kFoldConj>(u);
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[b + B * r] = u[r];
-    }
+    load_tw<PASS + 1>(tw, t, wn);
+    butterflies<PASS, CJ>(v, w, leaf);
     if constexpr (!LAST) {
       typedef Pad<LOG2N, PASS, PLAN> Out;
       static_assert(pad_splits<Out, G::N, R, NS>(), "padded offsets of a butterfly must not straddle a pad");
@@ -286,25 +323,16 @@ struct Engine {
   }
 
   // Full forward transform: v[e] = x[t + T e] in, v[e] = X[t + T e] out
-  // (CJ: conj(X[t + T e]), see kFoldConj).
-  template <bool CJ = false>
+  // (CJ: conj(X[t + T e])).
+  template <bool CJ = false, class Leaf = LeafPlain>
   static __device__ __forceinline__ void run(Comp (&v)[E], Lds *lds, const Tw *__restrict__ tw,
-                                             int t) {
-    Tw w[E];
-    load_tw<1>(tw, t, w);
-    pass<0, true, CJ>(v, lds, tw, t, w);
-    if constexpr (G::S::P > 1) pass<1, true, CJ>(v, lds, tw, t, w);
-    if constexpr (G::S::P > 2) pass<2, true, CJ>(v, lds, tw, t, w);
-    if constexpr (G::S::P > 3) pass<3, true, CJ>(v, lds, tw, t, w);
+                                             int t, Leaf leaf = Leaf{}) {
+    Tw w[4][TWN];  // row sets of passes 1 .. 3, each live for a pass and a half
+    pass<0, CJ>(v, lds, tw, t, w[0], w[1], leaf);
+    if constexpr (G::S::P > 1) pass<1, CJ>(v, lds, tw, t, w[1], w[2], leaf);
+    if constexpr (G::S::P > 2) pass<2, CJ>(v, lds, tw, t, w[2], w[3], leaf);
+    if constexpr (G::S::P > 3) pass<3, CJ>(v, lds, tw, t, w[3], w[0], leaf);
     conj_unfolded<CJ>(v);
-  }
-
-  template <bool CJ>
-  static __device__ __forceinline__ void conj_unfolded(Comp (&v)[E]) {
-    if constexpr (CJ && !kFoldConj) {
-#pragma unroll
-      for (int e = 0; e < E; ++e) v[e] = conj_store(v[e]);
-    }
   }
 
   // ---- twiddles held in registers for a whole persistent kernel ----
@@ -316,7 +344,7 @@ struct Engine {
   // most 3 passes.
   static constexpr bool kTwRegs = sizeof(Tw) == 4 && sizeof(Comp) == 4 && G::S::P <= 3;
   struct TwRegs {
-    Tw w[G::S::P > 1 ? G::S::P - 1 : 1][E];
+    Tw w[G::S::P > 1 ? G::S::P - 1 : 1][TWN];
   };
   static __device__ __forceinline__ void load_tw_regs(const Tw *__restrict__ tw, int t, TwRegs &W) {
     if constexpr (G::S::P > 1) load_tw<1>(tw, t, W.w[0]);
@@ -328,9 +356,9 @@ struct Engine {
   // previous reads of buf[x & 1] belong to the gather after exchange x - 2,
   // which every wave finished before reaching the barrier of exchange x - 1,
   // so one barrier per exchange (after the writes) orders everything.
-  template <int PASS, bool CJ = false>
+  template <int PASS, bool CJ, class Leaf>
   static __device__ __forceinline__ void pass_db(Comp (&v)[E], Lds *const (&buf)[2], unsigned &x,
-                                                 int t, const Tw (&w)[E]) {
+                                                 int t, const Tw (&w)[TWN], Leaf leaf) {
     constexpr int R = G::radix(PASS);
     constexpr int NS = G::span(PASS);
     constexpr int B = E / R;
@@ -342,22 +370,9 @@ struct Engine {
       const int tp = In::at(t);
 #pragma unroll
       for (int e = 0; e < E; ++e) raw[e] = rd[lds_slot<In, T>(tp, e)];
-#pragma unroll
-      for (int b = 0; b < B; ++b) {
-        v[b] = M::from_lds(raw[b]);
-#pragma unroll
-        for (int r = 1; r < R; ++r) v[b + B * r] = M::twiddle(raw[b + B * r], w[b * R + r]);
-      }
+      gather<PASS>(v, raw, w);
     }
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-      Comp u[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) u[r] = v[b + B * r];
-      dft<R, CJ && LAST && kFoldConj>(u);
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[b + B * r] = u[r];
-    }
+    butterflies<PASS, CJ>(v, w, leaf);
     if constexpr (!LAST) {
       typedef Pad<LOG2N, PASS, PLAN> Out;
       static_assert(pad_splits<Out, G::N, R, NS>(), "padded offsets of a butterfly must not straddle a pad");
@@ -382,9 +397,9 @@ struct Engine {
   // barrier per exchange); NB = 1: one buffer, a barrier before its writes
   // too.  MID() runs between the twiddle products and the butterflies (the
   // next pass's twiddle loads, where twiddles come from memory).
-  template <int PASS, bool CJ, int RR, int NB, class Mid>
+  template <int PASS, bool CJ, int RR, int NB, class Leaf, class Mid>
   static __device__ __forceinline__ void pass_rr(Comp (&v)[RR][E], Lds *const (&buf)[2], unsigned &x,
-                                                 int t, const Tw (&w)[E], Mid mid) {
+                                                 int t, const Tw (&w)[TWN], Leaf leaf, Mid mid) {
     constexpr int R = G::radix(PASS);
     constexpr int NS = G::span(PASS);
     constexpr int B = E / R;
@@ -398,27 +413,12 @@ struct Engine {
         Lds raw[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) raw[e] = rd[q * G::LDS_N + lds_slot<In, T>(tp, e)];
-#pragma unroll
-        for (int b = 0; b < B; ++b) {
-          v[q][b] = M::from_lds(raw[b]);
-#pragma unroll
-          for (int r = 1; r < R; ++r) v[q][b + B * r] = M::twiddle(raw[b + B * r], w[b * R + r]);
-        }
+        gather<PASS>(v[q], raw, w);
       }
     }
     mid();
 #pragma unroll
-    for (int q = 0; q < RR; ++q) {
-#pragma unroll
-      for (int b = 0; b < B; ++b) {
-        Comp u[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) u[r] = v[q][b + B * r];
-        dft<R, CJ && LAST && kFoldConj>(u);
-#pragma unroll
-        for (int r = 0; r < R; ++r) v[q][b + B * r] = u[r];
-      }
-    }
+    for (int q = 0; q < RR; ++q) butterflies<PASS, CJ>(v[q], w, leaf);
     if constexpr (!LAST) {
       typedef Pad<LOG2N, PASS, PLAN> Out;
       static_assert(pad_splits<Out, G::N, R, NS>(), "padded offsets of a butterfly must not straddle a pad");
@@ -439,51 +439,42 @@ struct Engine {
     }
   }
 
-  template <bool CJ, int RR>
-  static __device__ __forceinline__ void conj_unfolded_rr(Comp (&v)[RR][E]) {
-    if constexpr (CJ && !kFoldConj) {
-#pragma unroll
-      for (int q = 0; q < RR; ++q)
-#pragma unroll
-        for (int e = 0; e < E; ++e) v[q][e] = conj_store(v[q][e]);
-    }
-  }
-
   // RR rows with register twiddles, NB buffers per row (2: one barrier per
   // exchange; 1: two).
-  template <bool CJ, int RR, int NB = 2>
+  template <bool CJ, int RR, int NB = 2, class Leaf = LeafPlain>
   static __device__ __forceinline__ void run_regs_rr(Comp (&v)[RR][E], Lds *const (&buf)[2], unsigned &x,
-                                                     int t, TwRegs &W) {
+                                                     int t, TwRegs &W, Leaf leaf = Leaf{}) {
     static_assert(kTwRegs, "register twiddles need packed FP16 data and twiddles and at most 3 passes");
     auto none = [] {};
-    pass_rr<0, CJ, RR, NB>(v, buf, x, t, W.w[0], none);
-    if constexpr (G::S::P > 1) pass_rr<1, CJ, RR, NB>(v, buf, x, t, W.w[0], none);
-    if constexpr (G::S::P > 2) pass_rr<2, CJ, RR, NB>(v, buf, x, t, W.w[1], none);
-    conj_unfolded_rr<CJ>(v);
+    pass_rr<0, CJ, RR, NB>(v, buf, x, t, W.w[0], leaf, none);
+    if constexpr (G::S::P > 1) pass_rr<1, CJ, RR, NB>(v, buf, x, t, W.w[0], leaf, none);
+    if constexpr (G::S::P > 2) pass_rr<2, CJ, RR, NB>(v, buf, x, t, W.w[1], leaf, none);
+#pragma unroll
+    for (int q = 0; q < RR; ++q) conj_unfolded<CJ>(v[q]);
   }
 
   // RR rows with twiddles loaded from the plan's table one pass ahead.
-  template <bool CJ, int RR, int NB>
+  template <bool CJ, int RR, int NB, class Leaf = LeafPlain>
   static __device__ __forceinline__ void run_rr(Comp (&v)[RR][E], Lds *const (&buf)[2], unsigned &x,
-                                                const Tw *__restrict__ tw, int t) {
-    Tw w[E];
-    load_tw<1>(tw, t, w);
-    pass_rr<0, CJ, RR, NB>(v, buf, x, t, w, [] {});
-    if constexpr (G::S::P > 1) pass_rr<1, CJ, RR, NB>(v, buf, x, t, w, [&] { load_tw<2>(tw, t, w); });
-    if constexpr (G::S::P > 2) pass_rr<2, CJ, RR, NB>(v, buf, x, t, w, [&] { load_tw<3>(tw, t, w); });
-    if constexpr (G::S::P > 3) pass_rr<3, CJ, RR, NB>(v, buf, x, t, w, [] {});
-    conj_unfolded_rr<CJ>(v);
+                                                const Tw *__restrict__ tw, int t, Leaf leaf = Leaf{}) {
+    Tw w[4][TWN];
+    pass_rr<0, CJ, RR, NB>(v, buf, x, t, w[0], leaf, [&] { load_tw<1>(tw, t, w[1]); });
+    if constexpr (G::S::P > 1) pass_rr<1, CJ, RR, NB>(v, buf, x, t, w[1], leaf, [&] { load_tw<2>(tw, t, w[2]); });
+    if constexpr (G::S::P > 2) pass_rr<2, CJ, RR, NB>(v, buf, x, t, w[2], leaf, [&] { load_tw<3>(tw, t, w[3]); });
+    if constexpr (G::S::P > 3) pass_rr<3, CJ, RR, NB>(v, buf, x, t, w[3], leaf, [] {});
+#pragma unroll
+    for (int q = 0; q < RR; ++q) conj_unfolded<CJ>(v[q]);
   }
 
   // Forward transform with register twiddles and two LDS buffers (CJ as in
   // run).
-  template <bool CJ = false>
+  template <bool CJ = false, class Leaf = LeafPlain>
   static __device__ __forceinline__ void run_regs(Comp (&v)[E], Lds *const (&buf)[2], unsigned &x,
-                                                  int t, TwRegs &W) {
+                                                  int t, TwRegs &W, Leaf leaf = Leaf{}) {
     static_assert(kTwRegs, "register twiddles need packed FP16 data and twiddles and at most 3 passes");
-    pass_db<0, CJ>(v, buf, x, t, W.w[0]);
-    if constexpr (G::S::P > 1) pass_db<1, CJ>(v, buf, x, t, W.w[0]);
-    if constexpr (G::S::P > 2) pass_db<2, CJ>(v, buf, x, t, W.w[1]);
+    pass_db<0, CJ>(v, buf, x, t, W.w[0], leaf);
+    if constexpr (G::S::P > 1) pass_db<1, CJ>(v, buf, x, t, W.w[0], leaf);
+    if constexpr (G::S::P > 2) pass_db<2, CJ>(v, buf, x, t, W.w[1], leaf);
     conj_unfolded<CJ>(v);
   }
 };

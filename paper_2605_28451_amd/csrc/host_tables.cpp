@@ -120,18 +120,34 @@ void encode_complex(const std::complex<double> *src, size_t count, int fmt, void
 }
 
 // --------------------------------------------------------- twiddles -------
-// Pass p of a size with radices R_0..R_{P-1}: span NS_p = R_0 ... R_{p-1};
-// entries W_{NS R}^{m r} = W_N^{m r N / (NS R)} for m < NS, r < R, stored
-// row-major by m, passes with NS > 1 concatenated in order.
-std::vector<std::complex<double>> twiddle_table(int log2n, const int *radix, int passes) {
+// Pass p of a size with radices R_0..R_{P-1}: span NS_p = R_0 ... R_{p-1},
+// one row per m < NS, row-major by m, passes with NS > 1 concatenated in
+// order.  merged = false: entries W_{NS R}^{m r}, r < R.  merged = true: the
+// R / 2 entries that decimation in time merges into the butterflies, level
+// L = R first, then L = R / 2 ... 2: with w = W_{NS R}^{m R / L} W_L^k,
+// k < max(L / 4, 1),
+//   L >= 8, k < L / 8: (g, t) of w = g (1 + i t); other k: of w = g (t + i);
+//   L = 4 and 2: (Re w, Im w).
+std::vector<std::complex<double>> twiddle_table(int log2n, const int *radix, int passes, bool merged) {
   const long long n = 1ll << log2n;
   std::vector<std::complex<double>> t;
   long long ns = radix[0];
   for (int p = 1; p < passes; ++p) {
     const int r_p = radix[p];
     const long long stride = n / (ns * r_p);
-    for (long long m = 0; m < ns; ++m)
-      for (int r = 0; r < r_p; ++r) t.push_back(unit_root(m * r * stride, n));
+    for (long long m = 0; m < ns; ++m) {
+      if (!merged) {
+        for (int r = 0; r < r_p; ++r) t.push_back(unit_root(m * r * stride, n));
+        continue;
+      }
+      for (int l = r_p; l >= 2; l /= 2)
+        for (int k = 0; k < (l >= 4 ? l / 4 : 1); ++k) {
+          const std::complex<double> w = unit_root(m * (r_p / l) * stride + k * (n / l), n);
+          if (l < 8) t.push_back(w);
+          else if (k < l / 8) t.push_back({w.real(), w.imag() / w.real()});
+          else t.push_back({w.imag(), w.real() / w.imag()});
+        }
+    }
     ns *= r_p;
   }
   return t;

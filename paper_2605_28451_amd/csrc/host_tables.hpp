@@ -13,7 +13,7 @@ std::complex<double> unit_root(long long k, long long n);
 uint16_t f64_to_f16_bits(double x);
 uint8_t f64_to_fp8_bits(double x, int mant, int bias);
 void encode_complex(const std::complex<double> *src, size_t count, int fmt, void *dst);
-std::vector<std::complex<double>> twiddle_table(int log2n, const int *radix, int passes);
+std::vector<std::complex<double>> twiddle_table(int log2n, const int *radix, int passes, bool merged);
 void host_fft(std::vector<std::complex<double>> &a);
 std::vector<uint16_t> mfma4096_table();
 // Amplitude taper of `len` points for weighted matched filters (kind: 0

@@ -112,7 +112,7 @@ __device__ __forceinline__ int xcd_group(int it, int groups) {
 }
 
 // The image entropy sums of a workgroup: a fixed-order tree of the threads'
-// (S, Q) in `sh` (2 * WG doubles of LDS, free once the caller's barrier has
+// (S, Q / ln 2) in `sh` (2 * WG doubles of LDS, free once the caller's barrier has
 // passed), written as the workgroup's partial; a second kernel adds the
 // partials.  (Finishing the total in the workgroup that arrives last would
 // need a device-scope release per workgroup, an L2 writeback in the middle
@@ -131,7 +131,7 @@ __device__ __forceinline__ void entropy_sums(const RowArgs &a, double es, double
   }
   if (threadIdx.x == 0) {
     a.ent_partial[2 * blockIdx.x] = sh[0];
-    a.ent_partial[2 * blockIdx.x + 1] = sh[WG];
+    a.ent_partial[2 * blockIdx.x + 1] = sh[WG] * kLn2;
   }
 }
 
@@ -192,7 +192,7 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
   // rows keep the per-element decode, which needs fewer registers)
   constexpr bool kRowIo = !PIPE && sizeof(Store) >= 4;
   constexpr bool kHoist = sizeof(Filt) == 4 && OP != OP_FWD &&
-                          (LOG2N <= 12 || !std::is_same<M, ModeFP16>::value);
+                          (LOG2N <= 12 || !std::is_base_of<ModeFP16, M>::value);
   Filt hf[kHoist ? E : 1];
   if constexpr (kHoist) {
     if (f) {
@@ -216,14 +216,14 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
       for (int e = 0; e < E; ++e) nx[e] = ld_stream(src + (unsigned)(T * e));
     }
   }
-  auto transform = [&](Comp (&x)[E], unsigned tt) {
-    if constexpr (PIPE) EN::run_regs(x, buf, xch, tt, W);
-    else EN::run(x, lds, tw, tt);
+  auto transform = [&](Comp (&x)[E], unsigned tt, auto leaf) {
+    if constexpr (PIPE) EN::run_regs(x, buf, xch, tt, W, leaf);
+    else EN::run(x, lds, tw, tt, leaf);
   };
   // the inverse's transform, its final conjugate folded into the last pass
-  auto transform_conj = [&](Comp (&x)[E], unsigned tt) {
-    if constexpr (PIPE) EN::template run_regs<true>(x, buf, xch, tt, W);
-    else EN::template run<true>(x, lds, tw, tt);
+  auto transform_conj = [&](Comp (&x)[E], unsigned tt, auto leaf) {
+    if constexpr (PIPE) EN::template run_regs<true>(x, buf, xch, tt, W, leaf);
+    else EN::template run<true>(x, lds, tw, tt, leaf);
   };
   for (int it = blockIdx.x; it < groups; it += gridDim.x) {
   const int grp = group_of(it);
@@ -248,11 +248,13 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
 #pragma unroll
     for (int p = 0; p < (int)(sizeof(W.w) / sizeof(W.w[0])); ++p)
 #pragma unroll
-      for (int e = 0; e < E; ++e) asm volatile("" : "+v"(W.w[p][e]));
-    if constexpr (kHoist) {
+      for (int e = 0; e < EN::TWN; ++e) asm volatile("" : "+v"(W.w[p][e]));
+  }
+  // (and in the FP32-arithmetic modes converted, or as two product operands:
+  // 32 registers instead of 16)
+  if constexpr (kHoist) {
 #pragma unroll
-      for (int e = 0; e < E; ++e) asm volatile("" : "+v"(hf[e]));
-    }
+    for (int e = 0; e < E; ++e) asm volatile("" : "+v"(hf[e]));
   }
 
   Comp v[E];
@@ -295,9 +297,9 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
   }
 
   if constexpr (OP == OP_FWD) {
-    transform(v, tt);
+    transform(v, tt, M::first_leaf());
   } else {
-    if constexpr (OP == OP_COMPRESS) transform(v, tt);
+    if constexpr (OP == OP_COMPRESS) transform(v, tt, M::first_leaf());
     // BFP fold at the inverse's load: conj(z . H) . 2^-log2N, or with the
     // conjugated filter conj(z . conj H) = conj(z) . H
     constexpr int K = naive ? 0 : LOG2N;  // block shift 2^-log2N
@@ -337,7 +339,7 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
         if constexpr (kHoist) h = hf[e];
         else h = f[tt + T * e];
         filt_from_c32(cmul(to_c32(h), r), h);
-        v[e] = conj_pow2<K>(M::fmul(v[e], h));
+        v[e] = fold_in<K, E>(M::fmul(v[e], h), e);
         r = cmul(r, step);
       }
     } else if (OP == OP_COMPRESS || f) {
@@ -346,18 +348,18 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
         Filt h;
         if constexpr (kHoist) h = hf[e];
         else h = f[tt + T * e];
-        v[e] = conj_f ? pow2<K>(M::fmul(cconj(v[e]), h)) : conj_pow2<K>(M::fmul(v[e], h));
+        v[e] = conj_f ? fold_in<K, E, false>(M::fmul(cconj(v[e]), h), e) : fold_in<K, E>(M::fmul(v[e], h), e);
       }
     } else {
 #pragma unroll
-      for (int e = 0; e < E; ++e) v[e] = conj_pow2<K>(v[e]);
+      for (int e = 0; e < E; ++e) v[e] = fold_in<K, E>(v[e], e);
     }
     if constexpr (naive) {
-      transform(v, tt);
+      transform(v, tt, LeafPlain{});
 #pragma unroll
       for (int e = 0; e < E; ++e) v[e] = pow2<LOG2N>(M::round_store(cconj(v[e])));
     } else {
-      transform_conj(v, tt);
+      transform_conj(v, tt, fold_leaf<Comp, adapt ? 0 : K>());
     }
   }
   if constexpr (post) {
@@ -393,7 +395,7 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
           const c32 z = to_c32(v[e]);
           const float p = z.x * z.x + z.y * z.y;
           es += p;
-          eq += (double)p * (double)ln_pos(p);  // 0 ln 0 = 0: ln_pos(0) is finite
+          eq += (double)p * (double)log2_pos(p);  // 0 ln 0 = 0: log2_pos(0) is finite
         }
       }
     } else {
@@ -499,7 +501,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
 #pragma unroll
       for (int p = 0; p < (int)(sizeof(W.w) / sizeof(W.w[0])); ++p)
 #pragma unroll
-        for (int e = 0; e < E; ++e) asm volatile("" : "+v"(W.w[p][e]));
+        for (int e = 0; e < EN::TWN; ++e) asm volatile("" : "+v"(W.w[p][e]));
     }
     if constexpr (kHoist) {
 #pragma unroll
@@ -544,14 +546,14 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
         }
       }
     }
-    auto run = [&](auto cj) {
-      if constexpr (PIPE) EN::template run_regs_rr<decltype(cj)::value, RR, NB>(v, buf, xch, tt, W);
-      else EN::template run_rr<decltype(cj)::value, RR, NB>(v, buf, xch, tw, tt);
+    auto run = [&](auto cj, auto leaf) {
+      if constexpr (PIPE) EN::template run_regs_rr<decltype(cj)::value, RR, NB>(v, buf, xch, tt, W, leaf);
+      else EN::template run_rr<decltype(cj)::value, RR, NB>(v, buf, xch, tw, tt, leaf);
     };
     if constexpr (OP == OP_FWD) {
-      run(std::false_type{});
+      run(std::false_type{}, M::first_leaf());
     } else {
-      if constexpr (OP == OP_COMPRESS) run(std::false_type{});
+      if constexpr (OP == OP_COMPRESS) run(std::false_type{}, M::first_leaf());
       // BFP fold at the inverse's load: conj(z . H) . 2^-log2N, or with the
       // conjugated filter conj(z . conj H) = conj(z) . H
       if (OP == OP_COMPRESS || f) {
@@ -562,15 +564,16 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
           else h = f[tt + T * e];
 #pragma unroll
           for (int q = 0; q < RR; ++q)
-            v[q][e] = conj_f ? pow2<LOG2N>(M::fmul(cconj(v[q][e]), h)) : conj_pow2<LOG2N>(M::fmul(v[q][e], h));
+            v[q][e] = conj_f ? fold_in<LOG2N, E, false>(M::fmul(cconj(v[q][e]), h), e)
+                             : fold_in<LOG2N, E>(M::fmul(v[q][e], h), e);
         }
       } else {
 #pragma unroll
         for (int q = 0; q < RR; ++q)
 #pragma unroll
-          for (int e = 0; e < E; ++e) v[q][e] = conj_pow2<LOG2N>(v[q][e]);
+          for (int e = 0; e < E; ++e) v[q][e] = fold_in<LOG2N, E>(v[q][e], e);
       }
-      run(std::true_type{});
+      run(std::true_type{}, fold_leaf<Comp, LOG2N>());
     }
     unsigned bad = 0;
 #pragma unroll
@@ -588,7 +591,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
               const c32 z = to_c32(v[q][e]);
               const float p = z.x * z.x + z.y * z.y;
               es += p;
-              eq += (double)p * (double)ln_pos(p);
+              eq += (double)p * (double)log2_pos(p);
             }
           }
         } else {
@@ -766,11 +769,11 @@ static hipError_t launch_vector(const RowArgs &a, hipStream_t s) {
   unsigned grid = (unsigned)((a.rows + G::TPW - 1) / G::TPW);
   if (a.grid_limit > 0 && grid > (unsigned)a.grid_limit) grid = (unsigned)a.grid_limit;
   if constexpr ((V & V_ENT) != 0) {
-    static const unsigned occ = resident_per_cu(row_kernel<MODE, LOG2N, OP, V, OUT32, false>, G::WG);
+    static const unsigned occ = resident_per_cu(row_kernel<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, false>, G::WG);
     grid = image_grid<V>(a, grid, occ);
   }
   if (a.grid_out) *a.grid_out = (int)grid;
-  if constexpr (Engine<MODE, LOG2N>::kTwRegs) {
+  if constexpr (Engine<SizeMode<MODE, LOG2N>, LOG2N>::kTwRegs) {
     if (a.grid_limit > 0) {
       // pure FP16 at 4096 points: the pipelined kernel with one LDS buffer
       // (two barriers per exchange, 17 KiB: 5 workgroups per CU, as many as
@@ -780,13 +783,13 @@ static hipError_t launch_vector(const RowArgs &a, hipStream_t s) {
       constexpr bool kOneBuf = LOG2N == 12 && std::is_same<MODE, ModeFP16>::value && !OUT32 &&
                                (V & ~(V_CONJ | V_PHASOR)) == 0 && (!(V & V_PHASOR) || OP == OP_COMPRESS);
       if constexpr (kOneBuf)
-        hipLaunchKernelGGL((row_kernel_rr<MODE, LOG2N, OP, V, OUT32, 1, 1, true>), dim3(grid), dim3(G::WG), 0, s, a);
+        hipLaunchKernelGGL((row_kernel_rr<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, 1, 1, true>), dim3(grid), dim3(G::WG), 0, s, a);
       else
-        hipLaunchKernelGGL((row_kernel<MODE, LOG2N, OP, V, OUT32, true>), dim3(grid), dim3(G::WG), 0, s, a);
+        hipLaunchKernelGGL((row_kernel<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, true>), dim3(grid), dim3(G::WG), 0, s, a);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((row_kernel<MODE, LOG2N, OP, V, OUT32, false>), dim3(grid), dim3(G::WG), 0, s, a);
+  hipLaunchKernelGGL((row_kernel<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, false>), dim3(grid), dim3(G::WG), 0, s, a);
   return hipGetLastError();
 }
 
@@ -807,24 +810,24 @@ static bool launch_rr(const RowArgs &a, hipStream_t s, hipError_t &err) {
     // for 4096 x 4096 compressions, and the autofocus image 72-75 against
     // 80-85 us)
     constexpr long kSet = (long)G::TPW * RR * G::LDS_N * sizeof(typename MODE::Lds);
-    constexpr int NB = (Engine<MODE, LOG2N>::kTwRegs && 2 * kSet <= 80 * 1024) ? 2 : 1;
+    constexpr int NB = (Engine<SizeMode<MODE, LOG2N>, LOG2N>::kTwRegs && 2 * kSet <= 80 * 1024) ? 2 : 1;
     if constexpr (kSet > 80 * 1024) {
       return false;
     } else {
       if (a.rows_per_thread != 2) return false;
       unsigned grid = (unsigned)((a.rows + G::TPW * RR - 1) / (G::TPW * RR));
       if (a.grid_limit > 0 && grid > (unsigned)a.grid_limit) grid = (unsigned)a.grid_limit;
-      constexpr bool kPipe = Engine<MODE, LOG2N>::kTwRegs && NB == 2;
+      constexpr bool kPipe = Engine<SizeMode<MODE, LOG2N>, LOG2N>::kTwRegs && NB == 2;
       if constexpr ((V & V_ENT) != 0) {
         static const unsigned occ =
-            resident_per_cu(row_kernel_rr<MODE, LOG2N, OP, V, OUT32, RR, NB, false>, G::WG);
+            resident_per_cu(row_kernel_rr<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, RR, NB, false>, G::WG);
         grid = image_grid<V>(a, grid, occ);
       }
       if (a.grid_out) *a.grid_out = (int)grid;
       if (kPipe && a.grid_limit > 0)
-        hipLaunchKernelGGL((row_kernel_rr<MODE, LOG2N, OP, V, OUT32, RR, 2, kPipe>), dim3(grid), dim3(G::WG), 0, s, a);
+        hipLaunchKernelGGL((row_kernel_rr<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, RR, 2, kPipe>), dim3(grid), dim3(G::WG), 0, s, a);
       else
-        hipLaunchKernelGGL((row_kernel_rr<MODE, LOG2N, OP, V, OUT32, RR, NB, false>), dim3(grid), dim3(G::WG), 0, s, a);
+        hipLaunchKernelGGL((row_kernel_rr<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, RR, NB, false>), dim3(grid), dim3(G::WG), 0, s, a);
       err = hipGetLastError();
       return true;
     }
@@ -855,7 +858,7 @@ static bool launch_plan1(const RowArgs &a, hipStream_t s, hipError_t &err) {
       unsigned grid = (unsigned)((a.rows + G::TPW * RR - 1) / (G::TPW * RR));
       if (a.grid_limit > 0 && grid > (unsigned)a.grid_limit) grid = (unsigned)a.grid_limit;
       if (a.grid_out) *a.grid_out = (int)grid;
-      hipLaunchKernelGGL((row_kernel_rr<MODE, LOG2N, OP, V, OUT32, RR, NB, false, 1>), dim3(grid),
+      hipLaunchKernelGGL((row_kernel_rr<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, RR, NB, false, 1>), dim3(grid),
                          dim3(G::WG), 0, s, b);
       err = hipGetLastError();
     };

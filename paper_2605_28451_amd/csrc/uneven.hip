@@ -52,9 +52,10 @@ constexpr int UNEVEN_LDS = 16384 + 16384 / 16;  // largest per-item LDS (element
 // OFF32: the packed batch spans less than 4 GiB, so every access is a
 // uniform base plus a 32-bit byte offset (one 32-bit add per access instead
 // of a 64-bit address per lane).
-template <class M, int LOG2N, bool INV, bool OFF32>
-__device__ __forceinline__ void uneven_item(const UnevenArgs &a, int4 d, typename M::Lds *lds_all,
+template <class MODE0, int LOG2N, bool INV, bool OFF32>
+__device__ __forceinline__ void uneven_item(const UnevenArgs &a, int4 d, typename MODE0::Lds *lds_all,
                                             int tid) {
+  typedef SizeMode<MODE0, LOG2N> M;
   typedef Geometry<LOG2N> G;
   typedef Engine<M, LOG2N> EN;
   typedef typename M::Comp Comp;
@@ -90,7 +91,7 @@ __device__ __forceinline__ void uneven_item(const UnevenArgs &a, int4 d, typenam
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const Comp z = M::decode(ld_stream_g(g + ((unsigned)t + (unsigned)(T * k))));
-          v[e + k] = INV ? conj_pow2<LOG2N>(z) : z;  // BFP fold for inverse transforms
+          v[e + k] = INV ? fold_in<LOG2N, E>(z, e + k) : z;  // BFP fold for inverse transforms
         }
       }
     } else {
@@ -99,14 +100,16 @@ __device__ __forceinline__ void uneven_item(const UnevenArgs &a, int4 d, typenam
         Comp z;
         if constexpr (OFF32) z = M::decode(ld_stream_g((global_ptr<const Store>)(gb + (b0 + (unsigned)(T * e) * SZ))));
         else z = M::load(src, t + T * e);
-        v[e] = INV ? conj_pow2<LOG2N>(z) : z;
+        v[e] = INV ? fold_in<LOG2N, E>(z, e) : z;
       }
     }
   } else {
 #pragma unroll
     for (int e = 0; e < E; ++e) v[e] = Comp{};
   }
-  EN::template run<INV>(v, lds_all + local * G::LDS_N, static_cast<const typename M::Tw *>(a.tw[LOG2N - 8]), t);
+  const typename M::Tw *tw = static_cast<const typename M::Tw *>(a.tw[LOG2N - 8]);
+  if constexpr (INV) EN::template run<true>(v, lds_all + local * G::LDS_N, tw, t, fold_leaf<Comp, LOG2N>());
+  else EN::run(v, lds_all + local * G::LDS_N, tw, t, M::first_leaf());
   if (active) {
     Store *dst = static_cast<Store *>(a.out) + off;
     const global_ptr<char> gb = (global_ptr<char>)a.out;
