@@ -7,43 +7,53 @@
 namespace bfp {
 
 // ------------------------------------------------------------ corner turn --
-// out[c][r] = in[r][c].  A 256-thread workgroup moves a 64 x 64 tile: it is
-// read row by row (coalesced), staged in LDS with one element of padding per
-// row (so the column reads hit distinct banks), and written row by row of the
-// output.  Tiles are assigned row-major over the output so that consecutive
-// workgroups write neighbouring output rows.
+// out[c][r] = in[r][c].  A 256-thread workgroup moves a tile of 64 input rows
+// by TC input columns: it is read row by row (coalesced), staged in LDS with
+// one element of padding per row, and written row by row of the output.  Tiles
+// are assigned row-major over the output so that consecutive workgroups write
+// neighbouring output rows.  Each lane reads VL consecutive elements of an
+// input row and writes VS consecutive elements of an output row, each width
+// where that side's rows are whole, aligned chunks: a matrix with an odd
+// number of rows is still read 16 bytes per lane.  With TC = 128 each input
+// row segment is 512 bytes (4-byte elements), which measured 5% faster on
+// 4096 x 4096 than 64 x 64 tiles (25.0 against 26.4 us) although the staging
+// writes into LDS then meet 2-way bank conflicts; the reads out of LDS stay
+// conflict-free at the padded stride (bank of tile[r][c] = r + c mod 64).
 //
-// Vector form (rows and cols multiples of V, V elements = 8 or 16 bytes per
-// lane): each lane reads V consecutive elements of an input row and writes V
-// consecutive elements of an output row.  The tile is 64 input rows by TC
-// input columns: with TC = 128 each input row segment is 512 bytes (4-byte
-// elements), which measured 5% faster on 4096 x 4096 than 64 x 64 tiles
-// (25.0 against 26.4 us) although the staging writes into LDS then meet
-// 2-way bank conflicts; the reads out of LDS stay conflict-free at the
-// padded stride (bank of tile[r][c] = r + c mod 64).
-template <class T, int V, int TC = 64>
-__global__ void __launch_bounds__(256) transpose_vec_kernel(const T *__restrict__ in, T *__restrict__ out,
-                                                            int rows, int cols) {
-  typedef T vec __attribute__((ext_vector_type(V)));
-  constexpr int CH = TC / V;    // V-chunks per tile row
+// VS = 1: an output row starts anywhere in a cache line, so a tile's segment
+// shares its first and last lines with the neighbouring tiles of the row.
+// Those lines are merged in L2 (plain stores) where both tiles run on one
+// XCD: the tiles are dealt in runs of consecutive ones per XCD (workgroup w
+// runs on XCD w mod 8).
+template <class T, int VL, int VS, int TC>
+__global__ void __launch_bounds__(256) transpose_kernel(const T *__restrict__ in, T *__restrict__ out,
+                                                        int rows, int cols, int tiles) {
+  typedef T vin __attribute__((ext_vector_type(VL)));
+  typedef T vout __attribute__((ext_vector_type(VS)));
+  constexpr int CH = TC / VL;   // chunks per tile row
   constexpr int RPI = 256 / CH; // tile rows per iteration
-  constexpr int CHO = 64 / V;   // V-chunks per output row of the tile
+  constexpr int CHO = 64 / VS;  // chunks per output row of the tile
   constexpr int RPO = 256 / CHO;
   static_assert(256 % CH == 0 && 64 % RPI == 0 && TC % RPO == 0, "tile shape");
   __shared__ T tile[64][TC + 1];
   const int tiles_r = (rows + 63) / 64;
-  const int tc = blockIdx.x / tiles_r;
-  const int tr = blockIdx.x % tiles_r;
+  int b = blockIdx.x;
+  if constexpr (VS == 1) {
+    const int q = tiles >> 3, rem = tiles & 7, x = b & 7;
+    b = x * q + (x < rem ? x : rem) + (b >> 3);
+  }
+  const int tc = b / tiles_r;
+  const int tr = b % tiles_r;
   const int r0 = tr * 64, c0 = tc * TC;
   const int ch = threadIdx.x % CH, rl = threadIdx.x / CH;
 #pragma unroll
   for (int k = 0; k < 64 / RPI; ++k) {
     const int rr = rl + RPI * k;
-    const int r = r0 + rr, c = c0 + V * ch;
+    const int r = r0 + rr, c = c0 + VL * ch;
     if (r < rows && c < cols) {
-      const vec x = __builtin_nontemporal_load(reinterpret_cast<const vec *>(in + (size_t)r * cols + c));
+      const vin x = __builtin_nontemporal_load(reinterpret_cast<const vin *>(in + (size_t)r * cols + c));
 #pragma unroll
-      for (int u = 0; u < V; ++u) tile[rr][V * ch + u] = x[u];
+      for (int u = 0; u < VL; ++u) tile[rr][VL * ch + u] = x[u];
     }
   }
   __syncthreads();
@@ -51,117 +61,150 @@ __global__ void __launch_bounds__(256) transpose_vec_kernel(const T *__restrict_
 #pragma unroll
   for (int k = 0; k < TC / RPO; ++k) {
     const int oc = ro + RPO * k;      // output row within the tile = input column
-    const int orow = c0 + oc, ocol = r0 + V * cho;
+    const int orow = c0 + oc, ocol = r0 + VS * cho;
     if (orow < cols && ocol < rows) {
-      vec x;
+      vout x;
 #pragma unroll
-      for (int u = 0; u < V; ++u) x[u] = tile[V * cho + u][oc];
-      __builtin_nontemporal_store(x, reinterpret_cast<vec *>(out + (size_t)orow * rows + ocol));
+      for (int u = 0; u < VS; ++u) x[u] = tile[VS * cho + u][oc];
+      vout *dst = reinterpret_cast<vout *>(out + (size_t)orow * rows + ocol);
+      if constexpr (VS == 1) *dst = x;
+      else __builtin_nontemporal_store(x, dst);
     }
   }
 }
 
-// Element form for any shape.
-template <class T>
-__global__ void __launch_bounds__(256) transpose_kernel(const T *__restrict__ in, T *__restrict__ out,
-                                                        int rows, int cols) {
-  __shared__ T tile[64][65];
-  const int tiles_r = (rows + 63) / 64;
-  const int tc = blockIdx.x / tiles_r;  // tile column (input) = tile row of output
-  const int tr = blockIdx.x % tiles_r;
-  const int lane = threadIdx.x & 63;
-  const int wv = threadIdx.x >> 6;  // 0..3
-  const int r0 = tr * 64, c0 = tc * 64;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int r = r0 + wv + 4 * i, c = c0 + lane;
-    if (r < rows && c < cols) tile[wv + 4 * i][lane] = in[(size_t)r * cols + c];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int oc = c0 + wv + 4 * i;  // output row = input column
-    const int orr = r0 + lane;       // output column = input row
-    if (oc < cols && orr < rows) out[(size_t)oc * rows + orr] = tile[lane][wv + 4 * i];
-  }
+template <class T, int V, int TC>
+static hipError_t launch_transpose_of(const void *in, void *out, int rows, int cols, hipStream_t s) {
+  const long long tiles = (long long)((rows + 63) / 64) * ((cols + TC - 1) / TC);
+  if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+  const bool wide_in = cols % V == 0 && (uintptr_t)in % (V * sizeof(T)) == 0;
+  const bool wide_out = rows % V == 0 && (uintptr_t)out % (V * sizeof(T)) == 0;
+  const T *src = static_cast<const T *>(in);
+  T *dst = static_cast<T *>(out);
+  const dim3 grid((unsigned)tiles), block(256);
+  if (wide_in && wide_out)
+    hipLaunchKernelGGL((transpose_kernel<T, V, V, TC>), grid, block, 0, s, src, dst, rows, cols, (int)tiles);
+  else if (wide_in)
+    hipLaunchKernelGGL((transpose_kernel<T, V, 1, TC>), grid, block, 0, s, src, dst, rows, cols, (int)tiles);
+  else if (wide_out)
+    hipLaunchKernelGGL((transpose_kernel<T, 1, V, TC>), grid, block, 0, s, src, dst, rows, cols, (int)tiles);
+  else
+    hipLaunchKernelGGL((transpose_kernel<T, 1, 1, TC>), grid, block, 0, s, src, dst, rows, cols, (int)tiles);
+  return hipGetLastError();
 }
 
 hipError_t launch_transpose(const void *in, void *out, int rows, int cols, int bytes,
                             hipStream_t s) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
-  const long long tiles = (long long)((rows + 63) / 64) * ((cols + 63) / 64);
-  const long long tiles_w = (long long)((rows + 63) / 64) * ((cols + 127) / 128);  // 64 x 128 tiles
-  if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-  dim3 grid((unsigned)tiles), grid_w((unsigned)tiles_w), block(256);
-  // the vector form needs whole, aligned V-element chunks
-  const uintptr_t align = (uintptr_t)in | (uintptr_t)out;
   switch (bytes) {
-    case 2:
-      if (rows % 4 == 0 && cols % 4 == 0 && align % 8 == 0)
-        hipLaunchKernelGGL((transpose_vec_kernel<uint16_t, 4, 128>), grid_w, block, 0, s,
-                           (const uint16_t *)in, (uint16_t *)out, rows, cols);
-      else
-        hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, block, 0, s,
-                           (const uint16_t *)in, (uint16_t *)out, rows, cols);
-      break;
-    case 4:
-      if (rows % 4 == 0 && cols % 4 == 0 && align % 16 == 0)
-        hipLaunchKernelGGL((transpose_vec_kernel<uint32_t, 4, 128>), grid_w, block, 0, s,
-                           (const uint32_t *)in, (uint32_t *)out, rows, cols);
-      else
-        hipLaunchKernelGGL(transpose_kernel<uint32_t>, grid, block, 0, s,
-                           (const uint32_t *)in, (uint32_t *)out, rows, cols);
-      break;
-    case 8:
-      if (rows % 2 == 0 && cols % 2 == 0 && align % 16 == 0)
-        hipLaunchKernelGGL((transpose_vec_kernel<uint64_t, 2>), grid, block, 0, s,
-                           (const uint64_t *)in, (uint64_t *)out, rows, cols);
-      else
-        hipLaunchKernelGGL(transpose_kernel<uint2>, grid, block, 0, s, (const uint2 *)in,
-                           (uint2 *)out, rows, cols);
-      break;
-    default:
-      return hipErrorInvalidValue;
+    case 2: return launch_transpose_of<uint16_t, 4, 128>(in, out, rows, cols, s);
+    case 4: return launch_transpose_of<uint32_t, 4, 128>(in, out, rows, cols, s);
+    case 8: return launch_transpose_of<uint64_t, 2, 64>(in, out, rows, cols, s);
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 // ------------------------------------------------------------- convert ----
-__device__ __forceinline__ c32 load_fmt(const void *p, long long i, int fmt) {
-  switch (fmt) {
-    case 0: return static_cast<const c32 *>(p)[i];
-    case 1: return h2_to_c32(static_cast<const h2 *>(p)[i]);
-    case 2: return Fp8Codec<3>::decode2(static_cast<const uint16_t *>(p)[i]);
-    default: return Fp8Codec<2>::decode2(static_cast<const uint16_t *>(p)[i]);
+// Storage of one format: the complex element as stored, and its exact FP32
+// value.  FP32 -> FP16 rounds once (RNE); FP16/FP8 inputs are exact in FP32,
+// so every conversion is a single correct rounding of the input value.
+template <int FMT> struct Format;
+template <> struct Format<0> {
+  typedef c32 E;
+  static __device__ __forceinline__ c32 get(E e) { return e; }
+  static __device__ __forceinline__ E put(c32 v) { return v; }
+};
+template <> struct Format<1> {
+  typedef h2 E;
+  static __device__ __forceinline__ c32 get(E e) { return h2_to_c32(e); }
+  static __device__ __forceinline__ E put(c32 v) { return c32_to_h2(v); }
+};
+template <int MANT> struct FormatFp8 {
+  typedef uint16_t E;
+  static __device__ __forceinline__ c32 get(E e) { return Fp8Codec<MANT>::decode2(e); }
+  static __device__ __forceinline__ E put(c32 v) { return (E)Fp8Codec<MANT>::encode2(v.x, v.y); }
+};
+template <> struct Format<2> : FormatFp8<3> {};
+template <> struct Format<3> : FormatFp8<2> {};
+
+// V consecutive elements as one access
+template <class E, int V>
+struct alignas(V * sizeof(E)) Chunk {
+  E e[V];
+};
+
+// Bound by HBM: the formats are compile-time, a lane moves V = 2 elements per
+// access where both pointers are aligned for it (16 bytes of FP32, 8 of
+// FP16) and keeps kConvertUnroll loads in flight; the run-time format switch
+// per element that this replaces took 15.4 us for 1531 x 4096 FP32 -> FP16
+// (75 MB).
+constexpr int kConvertUnroll = 4;
+
+template <int IN, int OUT, int V>
+__global__ void __launch_bounds__(256) convert_kernel(const void *in, void *out, long long count) {
+  typedef Format<IN> I;
+  typedef Format<OUT> O;
+  typedef Chunk<typename I::E, V> CI;
+  typedef Chunk<typename O::E, V> CO;
+  const CI *src = static_cast<const CI *>(in);
+  CO *dst = static_cast<CO *>(out);
+  const long long chunks = count / V;
+  const long long step = 256LL * kConvertUnroll;
+  for (long long base = blockIdx.x * step + threadIdx.x; base < chunks; base += gridDim.x * step) {
+    CI x[kConvertUnroll];
+#pragma unroll
+    for (int u = 0; u < kConvertUnroll; ++u)
+      if (base + 256 * u < chunks) x[u] = src[base + 256 * u];
+#pragma unroll
+    for (int u = 0; u < kConvertUnroll; ++u)
+      if (base + 256 * u < chunks) {
+        CO y;
+#pragma unroll
+        for (int v = 0; v < V; ++v) y.e[v] = O::put(I::get(x[u].e[v]));
+        dst[base + 256 * u] = y;
+      }
+  }
+  if constexpr (V > 1) {  // the elements after the last whole chunk
+    const long long i = chunks * V + threadIdx.x;
+    if (blockIdx.x == 0 && i < count)
+      static_cast<typename O::E *>(out)[i] = O::put(I::get(static_cast<const typename I::E *>(in)[i]));
   }
 }
 
-// FP32 -> FP16 rounds once (RNE); FP16/FP8 inputs are exact in FP32, so
-// every conversion below is a single correct rounding of the input value.
-__device__ __forceinline__ void store_fmt(void *p, long long i, int fmt, c32 v) {
-  switch (fmt) {
-    case 0: static_cast<c32 *>(p)[i] = v; break;
-    case 1: static_cast<h2 *>(p)[i] = c32_to_h2(v); break;
-    case 2: static_cast<uint16_t *>(p)[i] = (uint16_t)Fp8Codec<3>::encode2(v.x, v.y); break;
-    default: static_cast<uint16_t *>(p)[i] = (uint16_t)Fp8Codec<2>::encode2(v.x, v.y); break;
-  }
+template <int IN, int OUT>
+static void launch_convert_of(const void *in, void *out, long long count, hipStream_t s) {
+  const bool wide = (uintptr_t)in % (2 * sizeof(typename Format<IN>::E)) == 0 &&
+                    (uintptr_t)out % (2 * sizeof(typename Format<OUT>::E)) == 0;
+  const long long per = 256LL * kConvertUnroll * (wide ? 2 : 1);
+  long long blocks = (count + per - 1) / per;
+  if (blocks > 65536) blocks = 65536;
+  const dim3 grid((unsigned)blocks), block(256);
+  if (wide) hipLaunchKernelGGL((convert_kernel<IN, OUT, 2>), grid, block, 0, s, in, out, count);
+  else hipLaunchKernelGGL((convert_kernel<IN, OUT, 1>), grid, block, 0, s, in, out, count);
 }
 
-__global__ void __launch_bounds__(256) convert_kernel(const void *in, int in_fmt, void *out,
-                                                      int out_fmt, long long count) {
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride)
-    store_fmt(out, i, out_fmt, load_fmt(in, i, in_fmt));
+template <int IN>
+static hipError_t launch_convert_from(const void *in, void *out, int out_fmt, long long count, hipStream_t s) {
+  switch (out_fmt) {
+    case 0: launch_convert_of<IN, 0>(in, out, count, s); break;
+    case 1: launch_convert_of<IN, 1>(in, out, count, s); break;
+    case 2: launch_convert_of<IN, 2>(in, out, count, s); break;
+    case 3: launch_convert_of<IN, 3>(in, out, count, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_convert(const void *in, int in_fmt, void *out, int out_fmt, long long count,
                           hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  long long blocks = (count + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(convert_kernel, dim3((unsigned)blocks), dim3(256), 0, s, in, in_fmt, out,
-                     out_fmt, count);
-  return hipGetLastError();
+  switch (in_fmt) {
+    case 0: return launch_convert_from<0>(in, out, out_fmt, count, s);
+    case 1: return launch_convert_from<1>(in, out, out_fmt, count, s);
+    case 2: return launch_convert_from<2>(in, out, out_fmt, count, s);
+    case 3: return launch_convert_from<3>(in, out, out_fmt, count, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 // -------------------------------------------------------------- phasor ----

@@ -145,6 +145,26 @@ def test_corner_turn_exact(fmt):
     assert np.array_equal(y, x.T)
 
 
+@pytest.mark.parametrize("fmt", ["fp16", "fp32", "e4m3"])
+@pytest.mark.parametrize("rows,cols", [(63, 128), (65, 260), (1531, 512), (260, 65), (4, 129), (127, 131), (1, 7),
+                                       (600, 1)])
+@pytest.mark.parametrize("off_in,off_out", [(0, 0), (1, 0), (0, 1), (2, 2)])
+def test_corner_turn_access_widths(fmt, rows, cols, off_in, off_out):
+    # each side takes wide accesses only where its rows are whole, aligned
+    # chunks: odd rows, odd columns and bases 1 or 2 elements off either side
+    need_gpu()
+    announce(f"corner turn widths {rows}x{cols} {fmt} offsets {off_in} {off_out}")
+    dt = api.TORCH_DTYPE[fmt]
+    x = torch.arange(rows * cols * 2, device="cuda").remainder(251).to(dt)
+    src = torch.empty(rows * cols * 2 + 8, dtype=dt, device="cuda")[2 * off_in:][:rows * cols * 2]
+    src.copy_(x)
+    buf = torch.full((rows * cols * 2 + 12,), 77, dtype=dt, device="cuda")
+    dst = buf[2 * off_out:][:rows * cols * 2].view(cols, rows, 2)
+    api.corner_turn(src.view(rows, cols, 2), fmt, out=dst)
+    assert torch.equal(dst, x.view(rows, cols, 2).transpose(0, 1))
+    assert bool((buf[:2 * off_out] == 77).all()) and bool((buf[2 * off_out + 2 * rows * cols:] == 77).all())
+
+
 @pytest.mark.parametrize("mode,n,rows", [("fp16", 4096, 300), ("fp16", 1024, 77), ("fp16", 4096, 4096),
                                          ("fp32", 4096, 65), ("fp16_mul_fp32_acc", 4096, 40),
                                          ("fp16_fp32", 512, 129), ("e4m3", 2048, 33)])
@@ -201,6 +221,24 @@ def test_convert_matches_host_encoder(src, dst):
     comp_nan = np.stack([np.isnan(dw.real), np.isnan(dw.imag)], -1)
     assert np.array_equal(np.where(comp_nan, 0, got), np.where(comp_nan, 0, want))
     assert comp_nan.any()
+
+
+@pytest.mark.parametrize("src,dst", [(a, b) for a in ("fp32", "fp16", "e4m3", "e5m2")
+                                     for b in ("fp32", "fp16", "e4m3", "e5m2")])
+@pytest.mark.parametrize("count,off", [(1, 0), (2, 0), (2047, 0), (2049, 1), (4097, 0), (300001, 0)])
+def test_convert_lengths_and_alignments(src, dst, count, off):
+    # two elements per access where both pointers allow it (off = 1: neither
+    # does), the element after the last whole pair, partly filled workgroups;
+    # the values of the element-wise definition, and nothing outside
+    need_gpu()
+    announce(f"convert {src}->{dst} count={count} off={off}")
+    v = scenes.quantize(np.random.default_rng(count).standard_normal(2 * count).view(complex) * 3.0, src)
+    x = upload(np.concatenate([np.zeros(off), v, np.zeros(3)]), src)[off:off + count]
+    buf = torch.full((count + 6, 2), 77, dtype=api.TORCH_DTYPE[dst], device="cuda")
+    out = buf[off:off + count]
+    api.convert(x, src, dst, out=out)
+    assert np.array_equal(download(out, dst), scenes.quantize(v, dst))
+    assert bool((buf[:off] == 77).all()) and bool((buf[off + count:] == 77).all())
 
 
 def _gpu_frame(sc, mode, phase=None):
