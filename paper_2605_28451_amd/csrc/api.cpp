@@ -692,11 +692,8 @@ int fft_plan_set_tuning(bfp_plan p, int engine, int blocks_per_cu) {
   if (blocks_per_cu < -1 || blocks_per_cu > 64)
     return fail(BFP_EINVAL, "blocks_per_cu must be -1 (automatic) or in [0, 64]");
   if (p->kind == 1 && blocks_per_cu < 0) return fail(BFP_EINVAL, "uneven plans take blocks_per_cu >= 0");
-  if (p->kind == 1) {
-    // above the resident maximum the hardware queues the extra workgroups
-    const int b = blocks_per_cu == 0 ? p->uneven_max_bpc : blocks_per_cu;
-    p->grid = b * p->cu_count;
-  }
+  // above the resident maximum the hardware queues the extra workgroups
+  if (p->kind == 1) p->grid = bfp::uneven_grid(p, blocks_per_cu);
   p->tune_engine = engine;
   p->tune_bpc = blocks_per_cu;
   return BFP_OK;

@@ -46,4 +46,7 @@ struct bfp_plan_s {
 namespace bfp {
 // Records msg as the calling thread's last error and returns status.
 int set_error(int status, const std::string &msg);
+// Workgroups of an uneven plan's launch for its blocks_per_cu knob (0: the
+// default of its mode).
+int uneven_grid(const bfp_plan_s *p, int blocks_per_cu);
 }  // namespace bfp

@@ -47,6 +47,18 @@ int table_for(int log2n, int prec, void **out) {
 
 }  // namespace
 
+// Pure FP16 takes one workgroup per tile: the hardware starts the next tile's
+// workgroup as one ends, without a queue claim between a tile's last store and
+// the next one's first load (149 against 164 us for the 20,000-transform
+// batch, 20.9 against 23.1 us for 2,000).  The other modes run one 1024-thread
+// workgroup per CU either way and measure alike to 2% slower (FP16 multiply:
+// 240 against 235 us), so they keep the resident grid and its queue.
+int bfp::uneven_grid(const bfp_plan_s *p, int blocks_per_cu) {
+  if (blocks_per_cu > 0) return blocks_per_cu * p->cu_count;
+  if (p->prec == BFP_FP16) return std::max(p->n_items, 1);
+  return p->uneven_max_bpc * p->cu_count;
+}
+
 extern "C" {
 
 int fft_plan_uneven(bfp_plan *out, int count, const int *log2n, const unsigned char *inverse,
@@ -132,7 +144,7 @@ int fft_plan_uneven(bfp_plan *out, int count, const int *log2n, const unsigned c
     else {
       p->cu_count = prop.multiProcessorCount;
       p->uneven_max_bpc = bfp::uneven_blocks_per_cu(prec);
-      p->grid = p->cu_count * p->uneven_max_bpc;
+      p->grid = bfp::uneven_grid(p, 0);
     }
   }
   if (st) {
