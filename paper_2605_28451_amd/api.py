@@ -24,13 +24,16 @@ def _prec(p):
 
 
 def _stream(stream=None):
+    # the raw handle: making a torch Stream object for it takes 2.9 us, the
+    # largest part of a small call (a 64 x 4096 forward transform: 9.1 us on
+    # the host, 6.2 without)
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def storage_format(precision) -> str:
