@@ -160,9 +160,7 @@ int fft_exec_inv_bfp_flags(bfp_plan p, const void *in, void *out, const void *fi
  * size; fft_autotune may still select 0).
  * blocks_per_cu: rows plans: -1 = automatic (the default of a new plan:
  * the fused compression of pure FP16 at n <= 4096 uses k = 3, or 8 from
- * 4096 rows of 4096 points; the FP32-output image of
- * sar_azimuth_image_entropy one round of its kernel's resident workgroups;
- * everything else 0), 0 = one workgroup per group of rows, k > 0 = a persistent grid of
+ * 4096 rows of 4096 points; everything else 0), 0 = one workgroup per group of rows, k > 0 = a persistent grid of
  * k workgroups per CU looping over the rows (in pure FP16 at n <= 4096 this
  * grid overlaps the next rows' loads with the current rows' transforms); uneven plans:
  * workgroups per CU of the launch, 0 = the default: in pure FP16 one
@@ -190,7 +188,8 @@ int fft_plan_get_tuning(bfp_plan p, int *engine, int *blocks_per_cu);
  * together, sharing twiddles and one barrier per LDS exchange; the other
  * variants, the matrix-core engine and sizes whose two rows would not leave
  * LDS for two workgroups per CU (FP32 exchanges above 4096 points, FP16
- * above 8192) ignore it.  For one radix plan, results are the same bits for
+ * above 8192) ignore it, and with automatic blocks_per_cu and radix_plan 0
+ * the library runs one row where that is faster.  For one radix plan, results are the same bits for
  * every engine-independent setting (blocks_per_cu, rows_per_thread).
  * Uneven plans take rows_per_thread = 1 and radix_plan = 0.  A new plan has
  * {1, -1, 2, 0} in the modes with FP32 arithmetic (BFP_FP32,

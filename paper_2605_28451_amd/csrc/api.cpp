@@ -28,10 +28,10 @@ namespace {
 // rows: the grid then outlasts one resident wave of workgroups), except for
 // the transposed store, whose XCD-aware row order wants the persistent grid
 // (a 4096 x 4096 frame with the fused corner turn: 156 us at 3, 166 us at
-// 8); the FP32-output image with its entropy sums one round of its kernel's
-// resident workgroups (sized in the launcher); every other operation one
-// workgroup per row group (the single transforms are faster at full
-// occupancy).
+// 8); every other operation one workgroup per row group (the single
+// transforms are faster at full occupancy, and the FP32 image with its
+// entropy sums, 4096 x 4096, takes 75.5 against 79 us on one round of
+// resident workgroups).
 constexpr int kAutoBpc = -1;
 constexpr int kPipelinedBpc = 3;
 constexpr int kPipelinedBpcLarge = 8;
@@ -44,14 +44,44 @@ int effective_bpc(const bfp_plan_s *p, int op, int rows, unsigned flags) {
 }
 
 
-// Rows per thread of a new plan: two in the modes with FP32 arithmetic,
-// where sharing twiddles and barriers between two rows is ~20% faster at
-// 2048 x 4096 (compression: FP16 storage 41.5 -> 33.5 us, FP32 48.8 -> 38.3,
-// E4M3 40.5 -> 31.4); one in pure FP16 and FP16-multiply, whose two-row
-// kernel is slower (17.8 -> 21.5 us, 26.3 -> 28.6: the 68 KiB of LDS of two
-// rows halves the workgroups per CU).
+// Rows per thread of a new plan: up to two in the modes with FP32 arithmetic
+// (auto_rows_per_thread), one in pure FP16 and FP16-multiply, whose two-row
+// kernel is slower (17.8 -> 21.5 us, 26.3 -> 28.6 for the 2048 x 4096
+// compression: the 68 KiB of LDS of two rows halves the workgroups per CU).
 int default_rows_per_thread(int prec) {
   return (prec == BFP_FP16 || prec == BFP_FP16_MUL_FP32_ACC) ? 1 : 2;
+}
+
+// rows_per_thread = 2 under automatic blocks_per_cu and radix plan 0: whether
+// an operation runs two rows per thread.  Two rows share twiddles and
+// barriers, one row doubles the workgroups and halves their registers and LDS.
+// With g one-row workgroups per CU (n = 256, 1024 and 4096 alike):
+//  - FP8 storage: one row, 5 to 60% faster at every size and g measured
+//    (compression of 2048 x 4096: 22.3 against 27.2 us).
+//  - FP16 storage, n >= 256: one row (compression of 64, 512, 2048 rows of
+//    4096: 6.4, 9.0, 22.5 against 9.5, 10.5, 25.1 us), but two for the plain
+//    forward transform from g = 8 on (n = 512 .. 4096: 19.6 against 15.9 us at
+//    2048 x 4096; 8.9 against 9.8 us at g = 4).
+//  - FP32, n >= 256: one row up to g = 2 (forward of 512 x 4096 7.7 against
+//    9.5 us; 64 rows 5.8 against 7.7).  Above, the compression takes two rows
+//    at n <= 512 (17.3 against 15.1 us for 16384 x 256) and one beyond (17.4
+//    against 18.1 for 1024 x 4096); the inverse with a filter two (29.8
+//    against 27.0 us at 2048 x 4096); the other single transforms two up to
+//    g = 4, a single round of one-row workgroups in which loads and
+//    arithmetic do not overlap (15.3 against 12.5 us at 1024 x 4096), and one
+//    beyond (26.1 against 28.3 at 2048 x 4096).
+//  - below 256 points (FP32 and FP16 storage) two.
+int auto_rows_per_thread(const bfp_plan_s *p, int op, int rows, bool filter) {
+  if (p->prec == BFP_FP8_E4M3_STORE || p->prec == BFP_FP8_E5M2_STORE) return 1;
+  if (p->log2n < 8) return 2;
+  const int t = bfp::threads_per_transform(p->log2n), per_wg = t < 256 ? 256 / t : 1;
+  const long long groups = ((long long)rows + per_wg - 1) / per_wg, cus = p->cu_count;
+  if (p->prec == BFP_FP16_STORE_FP32_COMPUTE)
+    return (op == bfp::OP_FWD && groups >= 8 * cus && p->log2n > 8 && p->log2n <= 12) ? 2 : 1;
+  if (groups <= 2 * cus) return 1;
+  if (op == bfp::OP_COMPRESS) return p->log2n <= 9 ? 2 : 1;
+  if (op == bfp::OP_INV && filter) return 2;
+  return groups <= 4 * cus ? 2 : 1;
 }
 
 thread_local std::string g_last_error;
@@ -207,11 +237,10 @@ int run_rows(bfp_plan p, int op, const void *in, void *out, const void *filter,
   a.nonfinite = p->nonfinite;
   const int bpc = effective_bpc(p, op, rows, flags);
   a.grid_limit = bpc > 0 ? bpc * p->cu_count : 0;
-  // the image with its entropy sums, under automatic tuning: one round of
-  // resident workgroups (the launcher sizes it for the kernel it launches)
-  a.resident_cus = (ent_partial && p->tune_bpc == kAutoBpc) ? p->cu_count : 0;
   a.engine = p->tune_engine;
   a.rows_per_thread = p->tune_rr;
+  if (p->tune_rr == 2 && p->tune_bpc == kAutoBpc && p->tune_plan == 0 && !ent_partial)
+    a.rows_per_thread = auto_rows_per_thread(p, op, rows, filter != nullptr);
   a.ent_partial = ent_partial;
   a.row_exp = row_exp;
   if (row_exp) a.flags |= bfp::KF_ADAPT;

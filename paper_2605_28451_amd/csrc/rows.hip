@@ -738,40 +738,11 @@ static hipError_t launch_mfma(const RowArgs &a, hipStream_t s) {
 }
 #endif
 
-// Workgroups of `kernel` (WG threads) resident on one CU, by the occupancy
-// calculator; at least 1.
-template <class K>
-static unsigned resident_per_cu(K kernel, int wg) {
-  int b = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kernel, wg, 0) != hipSuccess || b < 1) b = 1;
-  return (unsigned)b;
-}
-
-// The image-entropy variants (V_ENT) without a grid of their own
-// (a.resident_cus > 0): one round of the kernel's resident workgroups,
-// looping over the row groups (4096 x 4096 with FP16 storage: 66 against
-// 70-76 us for one workgroup per row pair); `occ` is the kernel's resident
-// count per CU.
-template <int V>
-static unsigned image_grid(const RowArgs &a, unsigned grid, unsigned occ) {
-  if constexpr ((V & V_ENT) != 0) {
-    if (a.grid_limit <= 0 && a.resident_cus > 0) {
-      const unsigned r = occ * (unsigned)a.resident_cus;
-      if (grid > r) grid = r;
-    }
-  }
-  return grid;
-}
-
 template <int LOG2N, int OP, int V, bool OUT32>
 static hipError_t launch_vector(const RowArgs &a, hipStream_t s) {
   typedef Geometry<LOG2N> G;
   unsigned grid = (unsigned)((a.rows + G::TPW - 1) / G::TPW);
   if (a.grid_limit > 0 && grid > (unsigned)a.grid_limit) grid = (unsigned)a.grid_limit;
-  if constexpr ((V & V_ENT) != 0) {
-    static const unsigned occ = resident_per_cu(row_kernel<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, false>, G::WG);
-    grid = image_grid<V>(a, grid, occ);
-  }
   if (a.grid_out) *a.grid_out = (int)grid;
   if constexpr (Engine<SizeMode<MODE, LOG2N>, LOG2N>::kTwRegs) {
     if (a.grid_limit > 0) {
@@ -818,11 +789,6 @@ static bool launch_rr(const RowArgs &a, hipStream_t s, hipError_t &err) {
       unsigned grid = (unsigned)((a.rows + G::TPW * RR - 1) / (G::TPW * RR));
       if (a.grid_limit > 0 && grid > (unsigned)a.grid_limit) grid = (unsigned)a.grid_limit;
       constexpr bool kPipe = Engine<SizeMode<MODE, LOG2N>, LOG2N>::kTwRegs && NB == 2;
-      if constexpr ((V & V_ENT) != 0) {
-        static const unsigned occ =
-            resident_per_cu(row_kernel_rr<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, RR, NB, false>, G::WG);
-        grid = image_grid<V>(a, grid, occ);
-      }
       if (a.grid_out) *a.grid_out = (int)grid;
       if (kPipe && a.grid_limit > 0)
         hipLaunchKernelGGL((row_kernel_rr<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, RR, 2, kPipe>), dim3(grid), dim3(G::WG), 0, s, a);

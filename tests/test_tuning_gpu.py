@@ -229,3 +229,30 @@ def test_uneven_grid_size_does_not_change_results():
     ms = plan.autotune_on(0, x, torch.empty_like(x), reps=3)
     assert ms > 0
     assert torch.equal(plan.execute(x), ref)
+
+
+@pytest.mark.parametrize("mode", ["fp32", "fp16_fp32", "e4m3"])
+@pytest.mark.parametrize("n", [64, 256, 512, 2048])
+def test_automatic_rows_per_thread_bits(mode, n):
+    # automatic tuning takes one or two rows per thread by operation, size and
+    # one-row workgroups per CU; on both sides of each line the results are
+    # the bits of either explicit setting
+    need_gpu()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    per_wg = {64: 64, 256: 16, 512: 4, 2048: 2}[n]
+    fmt = api.storage_format(mode)
+    top = 8 * cus * per_wg + 1
+    x = upload(0.25 * scenes.gaussian_rows(n, 97, n), fmt).repeat(top // 97 + 1, 1, 1)
+    rng = np.random.default_rng(n)
+    H = api.filter_tensor(rng.standard_normal(n) + 1j * rng.standard_normal(n), n, mode)
+    for rows in (1, 2 * cus * per_wg, 2 * cus * per_wg + 1, 4 * cus * per_wg, 4 * cus * per_wg + 1, top - 2, top):
+        announce(f"automatic rows per thread {mode} {rows}x{n}")
+        auto, plan = api.FFTPlan(n, rows, mode), api.FFTPlan(n, rows, mode)
+        xr = x[:rows].contiguous()
+        for op in ("forward", "inverse", "inverse_filter", "compress"):
+            run = {"forward": lambda p: p.forward(xr), "inverse": lambda p: p.inverse_bfp(xr),
+                   "inverse_filter": lambda p: p.inverse_bfp(xr, H), "compress": lambda p: p.range_compress(xr, H)}[op]
+            want = run(auto)
+            for rr in (1, 2):
+                plan.set_tuning_ex(1, 0, rr, 0)
+                assert torch.equal(run(plan), want), (op, rows, rr)
