@@ -151,6 +151,7 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
   typedef typename M::Filt Filt;
   typedef typename M::Tw Tw;
   constexpr int E = G::E, T = G::T, N = G::N;
+  constexpr bool kKeep = OP != OP_INV;  // outputs the next call reads (st_kept_g)
   constexpr bool naive = (V & V_NAIVE) != 0;
   constexpr bool conj_f = (V & V_CONJ) != 0;
   constexpr bool phasor = (V & V_PHASOR) != 0;
@@ -385,12 +386,12 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
       if constexpr (PIPE) {
         c32 *dst = static_cast<c32 *>(a.out) + row * N + tt;
 #pragma unroll
-        for (int e = 0; e < E; ++e) st_stream(dst + (unsigned)(T * e), to_c32(v[e]));
+        for (int e = 0; e < E; ++e) st_row<kKeep>(dst + (unsigned)(T * e), to_c32(v[e]));
       } else {
         c32 o[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) o[e] = to_c32(v[e]);
-        store_row<G>(a.out, row, tt & (T - 1), o);
+        store_row<G, kKeep>(a.out, row, tt & (T - 1), o);
       }
       if constexpr (ent) {
 #pragma unroll
@@ -405,12 +406,12 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
       if constexpr (!kRowIo) {
         Store *dst = static_cast<Store *>(a.out) + row * N + tt;
 #pragma unroll
-        for (int e = 0; e < E; ++e) M::store(dst, (unsigned)(T * e), v[e]);
+        for (int e = 0; e < E; ++e) st_row<kKeep>(dst + (unsigned)(T * e), M::encode(v[e]));
       } else {
         Store o[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) o[e] = M::encode(v[e]);
-        store_row<G>(a.out, row, tt & (T - 1), o);
+        store_row<G, kKeep>(a.out, row, tt & (T - 1), o);
       }
     }
     if (a.flags & KF_CHECK_FINITE) {
@@ -452,6 +453,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
   typedef typename M::Filt Filt;
   typedef typename M::Tw Tw;
   constexpr int E = G::E, T = G::T, N = G::N;
+  constexpr bool kKeep = OP != OP_INV;  // outputs the next call reads (st_kept_g)
   constexpr bool conj_f = (V & V_CONJ) != 0;
   constexpr bool phasor = (V & V_PHASOR) != 0;
   constexpr bool ent = (V & V_ENT) != 0;
@@ -586,7 +588,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
         if constexpr (OUT32) {
           c32 *dst = static_cast<c32 *>(a.out) + row * N + tt;
 #pragma unroll
-          for (int e = 0; e < E; ++e) st_stream(dst + (unsigned)(T * e), to_c32(v[q][e]));
+          for (int e = 0; e < E; ++e) st_row<kKeep>(dst + (unsigned)(T * e), to_c32(v[q][e]));
           if constexpr (ent) {
             // as in row_kernel: |I|^2 and |I|^2 ln |I|^2 in FP32, sums in FP64
 #pragma unroll
@@ -600,7 +602,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
         } else {
           Store *dst = static_cast<Store *>(a.out) + row * N + tt;
 #pragma unroll
-          for (int e = 0; e < E; ++e) M::store(dst, (unsigned)(T * e), v[q][e]);
+          for (int e = 0; e < E; ++e) st_row<kKeep>(dst + (unsigned)(T * e), M::encode(v[q][e]));
         }
         if (a.flags & KF_CHECK_FINITE) {
 #pragma unroll
