@@ -22,27 +22,30 @@ using bfp::RowArgs;
 namespace {
 
 // blocks_per_cu = kAutoBpc: the fused compression of pure FP16 up to n = 4096
-// runs the pipelined kernel on a grid of 3 workgroups per CU (4 fit, by
-// LDS; at 2048 rows of 4096, 3, 5 and 8 measure alike and 4 and 6 slower),
-// and of 8 per CU from 4096 rows of 4096 on (31.5 against 33.5 us at 4096
-// rows: the grid then outlasts one resident wave of workgroups), except for
-// the transposed store, whose XCD-aware row order wants the persistent grid
-// (a 4096 x 4096 frame with the fused corner turn: 156 us at 3, 166 us at
-// 8); every other operation one workgroup per row group (the single
+// runs the pipelined kernel on a persistent grid:
+//  - n = 4096: 5 workgroups per CU, as many as its registers let reside (1531
+//    rows 14.2 us against 15.3 at 3 per CU, 2048 rows 16.6 against 16.8 and
+//    17.3 at 8), and 8 where the rows outlast two rounds of those (4096 rows
+//    30.0 against 30.2 at 5 and 31.9 at 3, 3000 rows 24.1, 24.7, 26.2); 3 for
+//    the transposed store, whose XCD-aware row order wants few rows in flight
+//    (a 4096 x 4096 frame with the fused corner turn: 156 us at 3, 166 us at
+//    8);
+//  - n = 512, 8 values per thread: 16 (16384 rows 14.7 against 16.8 us at 3);
+//  - n = 256, 1024, 2048: 3 (4096 rows of 2048 17.0 against 17.2 us at 5, 8192
+//    of 1024 16.1 against 16.3).
+// Every other operation takes one workgroup per row group (the single
 // transforms are faster at full occupancy, and the FP32 image with its
 // entropy sums, 4096 x 4096, takes 75.5 against 79 us on one round of
 // resident workgroups).
 constexpr int kAutoBpc = -1;
-constexpr int kPipelinedBpc = 3;
-constexpr int kPipelinedBpcLarge = 8;
 
 int effective_bpc(const bfp_plan_s *p, int op, int rows, unsigned flags) {
   if (p->tune_bpc != kAutoBpc) return p->tune_bpc;
   if (op != bfp::OP_COMPRESS || p->prec != BFP_FP16 || p->log2n > 12 || p->log2n < 8) return 0;
-  const bool transposed = ((flags | p->flags) & BFP_FLAG_TRANSPOSED_STORE) != 0;
-  return (p->log2n == 12 && rows >= 4096 && !transposed) ? kPipelinedBpcLarge : kPipelinedBpc;
+  if ((flags | p->flags) & BFP_FLAG_TRANSPOSED_STORE) return 3;
+  if (p->log2n == 12) return rows > 2 * 5 * p->cu_count ? 8 : 5;
+  return p->log2n == 9 ? 16 : 3;
 }
-
 
 // Rows per thread of a new plan: up to two in the modes with FP32 arithmetic
 // (auto_rows_per_thread), one in pure FP16 and FP16-multiply, whose two-row
