@@ -60,15 +60,43 @@ enum Variant { V_PLAIN = 0, V_NAIVE = 1, V_CONJ = 2, V_PHASOR = 4, V_TRANS = 8, 
 // signed bin (k - N for k >= N/2), which is the band-limited (periodic sinc)
 // interpolation moving the compressed row s_r bins toward smaller range.
 // A thread's bins are k' = t + T e (e < E/2) and t + T e - N (e >= E/2), so
-// its phasors are base . step^e (times a wrap phasor for the upper half):
-// three sincospif per row (phases reduced to [-1/2, 1/2] cycles) and FP32
-// complex products (the error of 16 products stays below 1e-6); the product
-// with H is formed in FP32 and rounded once to the filter type.
+// its phasors are base . step^e (times a wrap phasor for the upper half),
+// sincospif of phases reduced to [-1/2, 1/2] cycles and FP32 complex products
+// (at most 8 in a row: their error stays below 1e-6); the product with H is
+// formed in FP32 and rounded once to the filter type.
+//
+// The phases are formed while the row's loads are in flight (taken after the
+// forward transform, the shift's load and the sines added their latency to
+// every row), step and wrap by one sincospif in pairs of lanes of one
+// transform, and the powers of step run as four chains instead of one.
 __device__ __forceinline__ c32 cycles_phasor(float cyc) {
   cyc -= rintf(cyc);
   float sn, cs;
   sincospif(2.0f * cyc, &sn, &cs);
   return c32{cs, sn};
+}
+// the value of the even (ODD = false) or odd lane of each pair, in both
+template <bool ODD>
+__device__ __forceinline__ float of_pair(float v) {
+  constexpr int quad = ODD ? 0xF5 : 0xA0;  // lanes (1, 1, 3, 3) or (0, 0, 2, 2)
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), quad, 0xf, 0xf, true));
+}
+struct Ramp {
+  c32 base, step, wrap;
+};
+template <int N, int T>
+__device__ __forceinline__ Ramp ramp_phasors(unsigned t, float sr) {
+  Ramp r;
+  r.base = cycles_phasor((float)t * sr * (1.0f / N));
+  if constexpr (T >= 2) {
+    const c32 w = cycles_phasor((threadIdx.x & 1) ? -sr : sr * ((float)T / N));
+    r.step = c32{of_pair<false>(w.x), of_pair<false>(w.y)};
+    r.wrap = c32{of_pair<true>(w.x), of_pair<true>(w.y)};
+  } else {
+    r.step = cycles_phasor(sr * ((float)T / N));
+    r.wrap = cycles_phasor(-sr);
+  }
+  return r;
 }
 __device__ __forceinline__ void filt_from_c32(c32 v, c32 &h) { h = v; }
 __device__ __forceinline__ void filt_from_c32(c32 v, h2 &h) { h = c32_to_h2(v); }
@@ -261,6 +289,8 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
     for (int e = 0; e < E; ++e) asm volatile("" : "+v"(hf[e]));
   }
 
+  float sr = 0.0f;
+  if constexpr (ramp) sr = active ? a.shift[row] : 0.0f;
   Comp v[E];
   if (active) {
     if constexpr (PIPE) {
@@ -282,6 +312,8 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
 #pragma unroll
     for (int e = 0; e < E; ++e) v[e] = Comp{};
   }
+  Ramp rp = {};
+  if constexpr (ramp) rp = ramp_phasors<N, T>(tt, sr);
   if constexpr (OP == OP_COMPRESS && phasor && !post) {
     if (active) {
       const c32 *ph = static_cast<const c32 *>(a.phasor) + tt;
@@ -332,19 +364,19 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
 #pragma unroll
       for (int e = 0; e < E; ++e) v[e] = conj_scale(v[e], sc);
     } else if constexpr (ramp) {
-      const float sr = active ? a.shift[row] : 0.0f;
-      c32 r = cycles_phasor((float)tt * sr * (1.0f / N));
-      const c32 step = cycles_phasor(sr * ((float)T / N));
-      const c32 wrap = cycles_phasor(-sr);
+      static_assert(E % 8 == 0, "four chains, the upper half on whole groups");
+      const c32 step2 = cmul(rp.step, rp.step), step4 = cmul(step2, step2);
+      const c32 up = cmul(step4, rp.wrap);  // into the upper half
+      c32 r[4] = {rp.base, cmul(rp.base, rp.step), cmul(rp.base, step2), {}};
+      r[3] = cmul(r[1], step2);
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        if (e == E / 2) r = cmul(r, wrap);
         Filt h;
         if constexpr (kHoist) h = hf[e];
         else h = f[tt + T * e];
-        filt_from_c32(cmul(to_c32(h), r), h);
+        filt_from_c32(cmul(to_c32(h), r[e & 3]), h);
         v[e] = fold_in<K, E>(M::fmul(v[e], h), e);
-        r = cmul(r, step);
+        if (e + 4 < E) r[e & 3] = cmul(r[e & 3], (e & ~3) + 4 == E / 2 ? up : step4);
       }
     } else if (OP == OP_COMPRESS || f) {
 #pragma unroll

@@ -419,6 +419,25 @@ def test_rcmc_compress_matches_oracle(mode, n, rows):
     assert s >= RCMC_SQNR_MIN[mode]
 
 
+@pytest.mark.parametrize("n,rows", [(8, 515), (16, 257), (32, 1), (64, 67), (512, 9), (1024, 5), (16384, 3)])
+def test_rcmc_compress_sizes(n, rows):
+    # one thread per transform (n <= 16), several transforms per wavefront and
+    # per workgroup, 8 and 16 values per thread, rows that leave transforms of
+    # a workgroup idle; FP32 against FP64 at the compression's bar
+    need_gpu()
+    announce(f"rcmc compress fp32 n={n} rows={rows}")
+    rng = np.random.default_rng(n)
+    x = scenes.quantize(scenes.gaussian_rows(n + 1, rows, n), "fp32")
+    shift = rng.uniform(-12.0, 12.0, rows).astype(np.float32)
+    h = scenes.range_replica_padded(n, max(n // 4, 2))
+    Hq = scenes.quantize(oracle.matched_filter(h, n), "fp32")
+    y = download(api.FFTPlan(n, rows, "fp32").range_compress_rcmc(
+        upload(x, "fp32"), api.filter_tensor(h, n, "fp32"), torch.from_numpy(shift).cuda()), "fp32")
+    # the step phase (below 1 cycle in size) rounds by 0.29 2^-24 cycles rms, 1.1e-7 rad, and enters up
+    # to 7 times (4.2 rms): 4.6e-7, 127 dB; 3 dB under it
+    assert sqnr_db(oracle.rcmc_compress(x, Hq, shift.astype(np.float64)), y) >= 124.0
+
+
 def _gpu_rcmc_frame(sc, mode):
     """azimuth FFT -> corner turn -> migration-corrected range compression
     per Doppler bin -> corner turn -> azimuth BFP inverse with H_a."""
