@@ -163,9 +163,9 @@ int fft_exec_inv_bfp_flags(bfp_plan p, const void *in, void *out, const void *fi
  * by size, everything else 0), 0 = one workgroup per group of rows, k > 0 = a persistent grid of
  * k workgroups per CU looping over the rows (in pure FP16 at n <= 4096 this
  * grid overlaps the next rows' loads with the current rows' transforms); uneven plans:
- * workgroups per CU of the launch, 0 = the default: in pure FP16 one
- * workgroup per tile, in the other modes the resident maximum (a persistent
- * grid whose workgroups pull tiles from the work queue), k in
+ * workgroups per CU of the launch, 0 = the default: one workgroup per tile in
+ * pure FP16, and in the other modes up to 4 tiles per CU; beyond, the resident
+ * maximum (a persistent grid whose workgroups pull tiles from the work queue), k in
  * [1, 64] = k per CU; above the resident maximum the hardware queues the
  * extra workgroups, and a grid with one workgroup per tile or more takes
  * every tile by workgroup index, without the queue.  Results do not depend

@@ -47,15 +47,17 @@ int table_for(int log2n, int prec, void **out) {
 
 }  // namespace
 
-// Pure FP16 takes one workgroup per tile: the hardware starts the next tile's
-// workgroup as one ends, without a queue claim between a tile's last store and
-// the next one's first load (149 against 164 us for the 20,000-transform
-// batch, 20.9 against 23.1 us for 2,000).  The other modes run one 1024-thread
-// workgroup per CU either way and measure alike to 2% slower (FP16 multiply:
-// 240 against 235 us), so they keep the resident grid and its queue.
+// One workgroup per tile lets the hardware start the next tile's workgroup as
+// one ends, without a queue claim between a tile's last store and the next
+// one's first load: in pure FP16 at every size (149 against 164 us for the
+// 20,000-transform batch, 20.9 against 23.1 us for 2,000), in the other modes,
+// which run one 1024-thread workgroup per CU either way, up to four rounds
+// (2,000 transforms, 570 tiles: 29.3 against 31.3 us with FP16 storage); the
+// 20,000-transform batch is 2.5% faster there on the resident grid and its
+// queue (225 against 230 us).
 int bfp::uneven_grid(const bfp_plan_s *p, int blocks_per_cu) {
   if (blocks_per_cu > 0) return blocks_per_cu * p->cu_count;
-  if (p->prec == BFP_FP16) return std::max(p->n_items, 1);
+  if (p->prec == BFP_FP16 || p->n_items <= 4 * p->cu_count) return std::max(p->n_items, 1);
   return p->uneven_max_bpc * p->cu_count;
 }
 
