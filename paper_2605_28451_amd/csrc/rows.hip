@@ -163,6 +163,16 @@ __device__ __forceinline__ void entropy_sums(const RowArgs &a, double es, double
   }
 }
 
+// Whether a row output of type X is stored so that the next call finds it in
+// the last-level cache (st_kept_g): every operation but the inverse, where the
+// T threads of a transform write at least 64 consecutive bytes per
+// instruction.  Below that the write-through sends each line on in several
+// parts: 16-point forward transforms of 200000 rows (FP16) took 47 us so
+// against 11 us with nontemporal stores, 128-point ones of 40000 rows (32
+// bytes) 16.7 against 12.3 us.
+template <int OP, int T, class X>
+constexpr bool keep_output = OP != OP_INV && T * sizeof(X) >= 64;
+
 // PIPE (persistent grids, where the engine keeps its twiddles in registers):
 // the twiddle rows are loaded once per workgroup, and the next row group's
 // data is loaded into registers while the current group is transformed, so
@@ -179,7 +189,6 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
   typedef typename M::Filt Filt;
   typedef typename M::Tw Tw;
   constexpr int E = G::E, T = G::T, N = G::N;
-  constexpr bool kKeep = OP != OP_INV;  // outputs the next call reads (st_kept_g)
   constexpr bool naive = (V & V_NAIVE) != 0;
   constexpr bool conj_f = (V & V_CONJ) != 0;
   constexpr bool phasor = (V & V_PHASOR) != 0;
@@ -239,13 +248,17 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
   typename EN::TwRegs W;
   Store nx[PIPE ? E : 1];
   auto group_of = [&](int it) { return trans ? xcd_group(it, groups) : it; };
+  // (nontemporal beside the transposed store, whose output lines wait in L2
+  // for their neighbours: plain loads push them out, 179 against 147 us for a
+  // 4096 x 4096 frame with the fused corner turn)
+  auto prefetch = [](const Store *p) { return trans ? ld_stream(p) : *p; };
   if constexpr (PIPE) {
     EN::load_tw_regs(tw, t, W);
     const long long row0 = (long long)group_of(blockIdx.x) * G::TPW + local;
     if ((int)blockIdx.x < groups && row0 < a.rows) {
       const Store *src = static_cast<const Store *>(a.in) + row0 * N + t;
 #pragma unroll
-      for (int e = 0; e < E; ++e) nx[e] = src[(unsigned)(T * e)];
+      for (int e = 0; e < E; ++e) nx[e] = prefetch(src + (unsigned)(T * e));
     }
   }
   auto transform = [&](Comp (&x)[E], unsigned tt, auto leaf) {
@@ -328,7 +341,7 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
     if (nrow < a.rows) {
       const Store *src = static_cast<const Store *>(a.in) + nrow * N + tt;
 #pragma unroll
-      for (int e = 0; e < E; ++e) nx[e] = src[(unsigned)(T * e)];
+      for (int e = 0; e < E; ++e) nx[e] = prefetch(src + (unsigned)(T * e));
     }
   }
 
@@ -418,12 +431,12 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
       if constexpr (PIPE) {
         c32 *dst = static_cast<c32 *>(a.out) + row * N + tt;
 #pragma unroll
-        for (int e = 0; e < E; ++e) st_row<kKeep>(dst + (unsigned)(T * e), to_c32(v[e]));
+        for (int e = 0; e < E; ++e) st_row<keep_output<OP, T, c32>>(dst + (unsigned)(T * e), to_c32(v[e]));
       } else {
         c32 o[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) o[e] = to_c32(v[e]);
-        store_row<G, kKeep>(a.out, row, tt & (T - 1), o);
+        store_row<G, keep_output<OP, T, c32>>(a.out, row, tt & (T - 1), o);
       }
       if constexpr (ent) {
 #pragma unroll
@@ -438,12 +451,12 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
       if constexpr (!kRowIo) {
         Store *dst = static_cast<Store *>(a.out) + row * N + tt;
 #pragma unroll
-        for (int e = 0; e < E; ++e) st_row<kKeep>(dst + (unsigned)(T * e), M::encode(v[e]));
+        for (int e = 0; e < E; ++e) st_row<keep_output<OP, T, Store>>(dst + (unsigned)(T * e), M::encode(v[e]));
       } else {
         Store o[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) o[e] = M::encode(v[e]);
-        store_row<G, kKeep>(a.out, row, tt & (T - 1), o);
+        store_row<G, keep_output<OP, T, Store>>(a.out, row, tt & (T - 1), o);
       }
     }
     if (a.flags & KF_CHECK_FINITE) {
@@ -485,7 +498,6 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
   typedef typename M::Filt Filt;
   typedef typename M::Tw Tw;
   constexpr int E = G::E, T = G::T, N = G::N;
-  constexpr bool kKeep = OP != OP_INV;  // outputs the next call reads (st_kept_g)
   constexpr bool conj_f = (V & V_CONJ) != 0;
   constexpr bool phasor = (V & V_PHASOR) != 0;
   constexpr bool ent = (V & V_ENT) != 0;
@@ -620,7 +632,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
         if constexpr (OUT32) {
           c32 *dst = static_cast<c32 *>(a.out) + row * N + tt;
 #pragma unroll
-          for (int e = 0; e < E; ++e) st_row<kKeep>(dst + (unsigned)(T * e), to_c32(v[q][e]));
+          for (int e = 0; e < E; ++e) st_row<keep_output<OP, T, c32>>(dst + (unsigned)(T * e), to_c32(v[q][e]));
           if constexpr (ent) {
             // as in row_kernel: |I|^2 and |I|^2 ln |I|^2 in FP32, sums in FP64
 #pragma unroll
@@ -634,7 +646,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
         } else {
           Store *dst = static_cast<Store *>(a.out) + row * N + tt;
 #pragma unroll
-          for (int e = 0; e < E; ++e) st_row<kKeep>(dst + (unsigned)(T * e), M::encode(v[q][e]));
+          for (int e = 0; e < E; ++e) st_row<keep_output<OP, T, Store>>(dst + (unsigned)(T * e), M::encode(v[q][e]));
         }
         if (a.flags & KF_CHECK_FINITE) {
 #pragma unroll
