@@ -173,6 +173,15 @@ __device__ __forceinline__ void entropy_sums(const RowArgs &a, double es, double
 template <int OP, int T, class X>
 constexpr bool keep_output = OP != OP_INV && T * sizeof(X) >= 64;
 
+// Wavefronts per SIMD to compile for (0: no constraint).  The forward
+// transform of 16384 points with FP16 on chip fits two 1024-thread workgroups
+// per CU if it keeps to 64 registers; with FP32 arithmetic (the FP16-multiply
+// mode) it took 72, 155 us for 4096 rows against 121 us at 64.
+template <class M, int LOG2N, int OP>
+constexpr int row_waves() {
+  return Geometry<LOG2N>::WG == 1024 && OP == OP_FWD && sizeof(typename M::Lds) == 4 ? 8 : 0;
+}
+
 // PIPE (persistent grids, where the engine keeps its twiddles in registers):
 // the twiddle rows are loaded once per workgroup, and the next row group's
 // data is loaded into registers while the current group is transformed, so
@@ -181,7 +190,7 @@ constexpr bool keep_output = OP != OP_INV && T * sizeof(X) >= 64;
 // of the caches faster (pure FP16, 2048 x 4096: 15.7 against 16.4 us with
 // nontemporal loads; the kernels that do not prefetch gain nothing from it).
 template <class M, int LOG2N, int OP, int V, bool OUT32, bool PIPE>
-__global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
+__global__ void __launch_bounds__((Geometry<LOG2N>::WG), (row_waves<M, LOG2N, OP>())) row_kernel(RowArgs a) {
   typedef Geometry<LOG2N> G;
   typedef Engine<M, LOG2N> EN;
   typedef typename M::Comp Comp;
