@@ -128,7 +128,7 @@ int upload_twiddles(int log2n, int prec, int plan, void **out) {
   int rad[4];
   const int passes = bfp::pass_count(log2n, plan);
   for (int p = 0; p < 4; ++p) rad[p] = bfp::pass_radix(log2n, plan, p);
-  const bool merged = bfp::merged_twiddles(prec, log2n);
+  const bool merged = bfp::merged_twiddles(prec);
   std::vector<std::complex<double>> t = bfp::twiddle_table(log2n, rad, passes, merged);
   if ((int)t.size() != bfp::twiddle_entries(log2n, plan, merged))
     return fail(BFP_EINVAL, "internal: twiddle table size mismatch");

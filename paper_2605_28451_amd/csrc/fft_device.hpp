@@ -354,7 +354,7 @@ __device__ __forceinline__ void dft(C (&x)[R], Leaf leaf = Leaf{}) {
 
 // ---------------------------------------------- DFTs after products ------
 // Packed FP16 DFTs by radix-4 steps, for the passes whose twiddles are
-// products ahead of the DFT (ModeFP16Products).  CJ returns the conjugated
+// products ahead of the DFT (ModeFP16).  CJ returns the conjugated
 // outputs: the last combining step takes conjugated operands (conj(x + y) =
 // conj x + conj y, conj(-i y) = i conj y), source negations of the packed
 // adds.
@@ -607,9 +607,13 @@ struct ModeFP32 {
   static __device__ __forceinline__ Comp round_store(Comp v) { return v; }
 };
 
-struct ModeFP16 {  // pure packed FP16
+// Pure packed FP16, twiddles as products ahead of radix-4 steps: a twiddle is
+// then one rounded pair of FP16 numbers.  Merged into the butterflies as the
+// two rounded factors of bf_tan it puts 2.5% (a transform of 8192 points), 3.1%
+// (16384) and 3.5% (a round trip of 16384) more error on the result.
+struct ModeFP16 {
   typedef h2 Store; typedef h2 Lds; typedef h2 Comp; typedef h2 Tw; typedef h2 Filt;
-  static constexpr bool kMerged = true, kTwice4 = false;
+  static constexpr bool kMerged = false, kTwice4 = false;
   static __device__ __forceinline__ LeafPlain first_leaf() { return LeafPlain{}; }
   static __device__ __forceinline__ Comp decode(Store s) { return s; }
   static __device__ __forceinline__ Store encode(Comp v) { return v; }
@@ -617,23 +621,10 @@ struct ModeFP16 {  // pure packed FP16
   static __device__ __forceinline__ void store(Store *p, unsigned i, Comp v) { st_stream(p + i, v); }
   static __device__ __forceinline__ Lds to_lds(Comp v) { return v; }
   static __device__ __forceinline__ Comp from_lds(Lds v) { return v; }
+  static __device__ __forceinline__ Comp twiddle(Lds v, Tw w) { return cmul(v, w); }
   static __device__ __forceinline__ Comp fmul(Comp v, Filt h) { return cmul(v, h); }
   static __device__ __forceinline__ Comp round_store(Comp v) { return v; }
 };
-
-// Pure FP16 with twiddles as products ahead of radix-4 steps: the sizes up to
-// 4096 points, whose fused compressions hold the twiddles in registers.  The
-// merged butterflies save 6% of the arithmetic there and no time (16.1 us
-// either way for the 2048 x 4096 compression, 31 us for 4096 x 4096); above,
-// where every pass reads the table, they take 103 instead of 110 us for a
-// forward and an inverse of 2047 x 16384.
-struct ModeFP16Products : ModeFP16 {
-  static constexpr bool kMerged = false;
-  static __device__ __forceinline__ Comp twiddle(Lds v, Tw w) { return cmul(v, w); }
-};
-// the arithmetic of a mode at a size (merged_twiddles() on the host)
-template <class M, int LOG2N>
-using SizeMode = std::conditional_t<std::is_same<M, ModeFP16>::value && LOG2N <= 12, ModeFP16Products, M>;
 
 __device__ __forceinline__ c32 h2_to_c32(h2 v) { return c32{(float)v.x, (float)v.y}; }
 

@@ -17,9 +17,9 @@
 // Twiddles come from a per-plan table in HBM (L2/L1-resident after the first
 // wavefronts), built on the host in FP64 and rounded once to the mode's
 // twiddle type: pass p owns a row for each m < NS, the R / 2 entries that the
-// merged butterflies of dft_tw take on base W_{NS R}^m, or, in the
-// FP16-multiply mode (products of FP16 operands ahead of the DFT), the R
-// entries W_{NS R}^{m r}.
+// merged butterflies of dft_tw take on base W_{NS R}^m, or, in the modes whose
+// twiddles are products ahead of the DFT (!kMerged), the R entries
+// W_{NS R}^{m r}.
 #pragma once
 
 #include <type_traits>

@@ -60,8 +60,8 @@ hipError_t launch_rows(int mode, int log2n, int op, bool out32, const RowArgs &a
 // (plan: 0 or 1, the radix plans of fft_engine.hpp; merged: the layout of the
 // arithmetic whose butterflies carry the twiddles)
 int twiddle_entries(int log2n, int plan, bool merged);
-// all but FP16-multiply, and pure FP16 up to 4096 points (SizeMode)
-inline bool merged_twiddles(int mode, int log2n) { return mode != 3 && !(mode == 1 && log2n <= 12); }
+// the modes' kMerged: all but pure FP16 and FP16-multiply
+inline bool merged_twiddles(int mode) { return mode != 1 && mode != 3; }
 int pass_count(int log2n, int plan = 0);
 int pass_radix(int log2n, int plan, int p);
 bool second_plan(int log2n);

@@ -242,7 +242,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N>::WG), (row_waves<M, LOG2N, OP
   // rows keep the per-element decode, which needs fewer registers)
   constexpr bool kRowIo = !PIPE && sizeof(Store) >= 4;
   constexpr bool kHoist = sizeof(Filt) == 4 && OP != OP_FWD &&
-                          (LOG2N <= 12 || !std::is_base_of<ModeFP16, M>::value);
+                          (LOG2N <= 12 || !std::is_same<M, ModeFP16>::value);
   Filt hf[kHoist ? E : 1];
   if constexpr (kHoist) {
     if (f) {
@@ -802,7 +802,7 @@ static hipError_t launch_vector(const RowArgs &a, hipStream_t s) {
   unsigned grid = (unsigned)((a.rows + G::TPW - 1) / G::TPW);
   if (a.grid_limit > 0 && grid > (unsigned)a.grid_limit) grid = (unsigned)a.grid_limit;
   if (a.grid_out) *a.grid_out = (int)grid;
-  if constexpr (Engine<SizeMode<MODE, LOG2N>, LOG2N>::kTwRegs) {
+  if constexpr (Engine<MODE, LOG2N>::kTwRegs) {
     if (a.grid_limit > 0) {
       // pure FP16 at 4096 points: the pipelined kernel with one LDS buffer
       // (two barriers per exchange, 17 KiB: 5 workgroups per CU, as many as
@@ -812,13 +812,13 @@ static hipError_t launch_vector(const RowArgs &a, hipStream_t s) {
       constexpr bool kOneBuf = LOG2N == 12 && std::is_same<MODE, ModeFP16>::value && !OUT32 &&
                                (V & ~(V_CONJ | V_PHASOR)) == 0 && (!(V & V_PHASOR) || OP == OP_COMPRESS);
       if constexpr (kOneBuf)
-        hipLaunchKernelGGL((row_kernel_rr<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, 1, 1, true>), dim3(grid), dim3(G::WG), 0, s, a);
+        hipLaunchKernelGGL((row_kernel_rr<MODE, LOG2N, OP, V, OUT32, 1, 1, true>), dim3(grid), dim3(G::WG), 0, s, a);
       else
-        hipLaunchKernelGGL((row_kernel<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, true>), dim3(grid), dim3(G::WG), 0, s, a);
+        hipLaunchKernelGGL((row_kernel<MODE, LOG2N, OP, V, OUT32, true>), dim3(grid), dim3(G::WG), 0, s, a);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((row_kernel<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, false>), dim3(grid), dim3(G::WG), 0, s, a);
+  hipLaunchKernelGGL((row_kernel<MODE, LOG2N, OP, V, OUT32, false>), dim3(grid), dim3(G::WG), 0, s, a);
   return hipGetLastError();
 }
 
@@ -839,19 +839,19 @@ static bool launch_rr(const RowArgs &a, hipStream_t s, hipError_t &err) {
     // for 4096 x 4096 compressions, and the autofocus image 72-75 against
     // 80-85 us)
     constexpr long kSet = (long)G::TPW * RR * G::LDS_N * sizeof(typename MODE::Lds);
-    constexpr int NB = (Engine<SizeMode<MODE, LOG2N>, LOG2N>::kTwRegs && 2 * kSet <= 80 * 1024) ? 2 : 1;
+    constexpr int NB = (Engine<MODE, LOG2N>::kTwRegs && 2 * kSet <= 80 * 1024) ? 2 : 1;
     if constexpr (kSet > 80 * 1024) {
       return false;
     } else {
       if (a.rows_per_thread != 2) return false;
       unsigned grid = (unsigned)((a.rows + G::TPW * RR - 1) / (G::TPW * RR));
       if (a.grid_limit > 0 && grid > (unsigned)a.grid_limit) grid = (unsigned)a.grid_limit;
-      constexpr bool kPipe = Engine<SizeMode<MODE, LOG2N>, LOG2N>::kTwRegs && NB == 2;
+      constexpr bool kPipe = Engine<MODE, LOG2N>::kTwRegs && NB == 2;
       if (a.grid_out) *a.grid_out = (int)grid;
       if (kPipe && a.grid_limit > 0)
-        hipLaunchKernelGGL((row_kernel_rr<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, RR, 2, kPipe>), dim3(grid), dim3(G::WG), 0, s, a);
+        hipLaunchKernelGGL((row_kernel_rr<MODE, LOG2N, OP, V, OUT32, RR, 2, kPipe>), dim3(grid), dim3(G::WG), 0, s, a);
       else
-        hipLaunchKernelGGL((row_kernel_rr<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, RR, NB, false>), dim3(grid), dim3(G::WG), 0, s, a);
+        hipLaunchKernelGGL((row_kernel_rr<MODE, LOG2N, OP, V, OUT32, RR, NB, false>), dim3(grid), dim3(G::WG), 0, s, a);
       err = hipGetLastError();
       return true;
     }
@@ -882,7 +882,7 @@ static bool launch_plan1(const RowArgs &a, hipStream_t s, hipError_t &err) {
       unsigned grid = (unsigned)((a.rows + G::TPW * RR - 1) / (G::TPW * RR));
       if (a.grid_limit > 0 && grid > (unsigned)a.grid_limit) grid = (unsigned)a.grid_limit;
       if (a.grid_out) *a.grid_out = (int)grid;
-      hipLaunchKernelGGL((row_kernel_rr<SizeMode<MODE, LOG2N>, LOG2N, OP, V, OUT32, RR, NB, false, 1>), dim3(grid),
+      hipLaunchKernelGGL((row_kernel_rr<MODE, LOG2N, OP, V, OUT32, RR, NB, false, 1>), dim3(grid),
                          dim3(G::WG), 0, s, b);
       err = hipGetLastError();
     };
