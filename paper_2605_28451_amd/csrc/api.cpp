@@ -58,33 +58,29 @@ int default_rows_per_thread(int prec) {
 // rows_per_thread = 2 under automatic blocks_per_cu and radix plan 0: whether
 // an operation runs two rows per thread.  Two rows share twiddles and
 // barriers, one row doubles the workgroups and halves their registers and LDS.
-// With g one-row workgroups per CU (n = 256, 1024 and 4096 alike):
-//  - FP8 storage: one row, 5 to 60% faster at every size and g measured
-//    (compression of 2048 x 4096: 22.3 against 27.2 us).
-//  - FP16 storage, n >= 256: one row (compression of 64, 512, 2048 rows of
-//    4096: 6.4, 9.0, 22.5 against 9.5, 10.5, 25.1 us), but two for the plain
-//    forward transform from g = 8 on (n = 512 .. 4096: 19.6 against 15.9 us at
-//    2048 x 4096; 8.9 against 9.8 us at g = 4).
-//  - FP32, n >= 256: one row up to g = 2 (forward of 512 x 4096 7.7 against
-//    9.5 us; 64 rows 5.8 against 7.7).  Above, the compression takes two rows
-//    at n <= 512 (17.3 against 15.1 us for 16384 x 256) and one beyond (17.4
-//    against 18.1 for 1024 x 4096); the inverse with a filter two (29.8
-//    against 27.0 us at 2048 x 4096); the other single transforms two up to
-//    g = 4, a single round of one-row workgroups in which loads and
-//    arithmetic do not overlap (15.3 against 12.5 us at 1024 x 4096), and one
-//    beyond (26.1 against 28.3 at 2048 x 4096).
-//  - below 256 points (FP32 and FP16 storage) two.
-int auto_rows_per_thread(const bfp_plan_s *p, int op, int rows, bool filter) {
-  if (p->prec == BFP_FP8_E4M3_STORE || p->prec == BFP_FP8_E5M2_STORE) return 1;
-  if (p->log2n < 8) return 2;
+// With g one-row workgroups per CU (figures one row / two rows, us):
+//  - FP32 and FP8, n >= 256: one row up to g = 2 (FP32 compressions of 64, 256
+//    and 512 rows of 4096: 7.9 / 11.9, 8.3 / 12.7, 12.9 / 13.9; forward 6.4 /
+//    7.8, 6.4 / 8.7, 9.2 / 9.6), two from there (1024 rows 24.7 / 18.9, 17.2 /
+//    14.2; 2048 rows 46.2 / 35.1, 30.1 / 28.8; E4M3 2048 rows 37.4 / 29.2, 20.0
+//    / 18.8): the reads of the twiddle table, one pair of floats per value,
+//    bind the one-row kernel.  (At g = 3 and, for single transforms, from g =
+//    16 on the two lie within 8% either way.)
+//  - FP8, n < 256: one row (E4M3 compression of 65536 x 128 27.3 / 32.8, of
+//    131072 x 64 33.2 / 34.5), but two with FP32 outputs from g = 2 on (40.8 /
+//    34.4 for 131072 x 64).  FP32, n < 256: two.
+//  - FP16 storage, n >= 256 (half the table, merged into the butterflies): one
+//    row (compression of 64, 512, 2048 rows of 4096: 6.4 / 9.5, 9.0 / 10.5,
+//    22.5 / 25.1), but two for the plain forward transform from g = 8 on (n =
+//    512 .. 4096: 19.6 / 15.9 at 2048 x 4096; 8.9 / 9.8 at g = 4); n < 256: two.
+int auto_rows_per_thread(const bfp_plan_s *p, int op, int rows, bool out32) {
+  const bool fp16 = p->prec == BFP_FP16_STORE_FP32_COMPUTE, fp32 = p->prec == BFP_FP32;
+  if (p->log2n < 8 && (fp16 || fp32)) return 2;
+  if (p->log2n < 8 && !out32) return 1;
   const int t = bfp::threads_per_transform(p->log2n), per_wg = t < 256 ? 256 / t : 1;
   const long long groups = ((long long)rows + per_wg - 1) / per_wg, cus = p->cu_count;
-  if (p->prec == BFP_FP16_STORE_FP32_COMPUTE)
-    return (op == bfp::OP_FWD && groups >= 8 * cus && p->log2n > 8 && p->log2n <= 12) ? 2 : 1;
-  if (groups <= 2 * cus) return 1;
-  if (op == bfp::OP_COMPRESS) return p->log2n <= 9 ? 2 : 1;
-  if (op == bfp::OP_INV && filter) return 2;
-  return groups <= 4 * cus ? 2 : 1;
+  if (fp16) return (op == bfp::OP_FWD && groups >= 8 * cus && p->log2n > 8 && p->log2n <= 12) ? 2 : 1;
+  return groups <= 2 * cus ? 1 : 2;
 }
 
 thread_local std::string g_last_error;
@@ -123,12 +119,13 @@ int log2_exact(long long n) {
 namespace {
 
 // The twiddle table of radix plan `plan` (the matrix-core operands first
-// where the mode and size have that engine, plan 0 only).
-int upload_twiddles(int log2n, int prec, int plan, void **out) {
+// where the mode and size have that engine, plan 0 only); products: for
+// twiddles as products also in a mode whose butterflies carry them.
+int upload_twiddles(int log2n, int prec, int plan, void **out, bool products = false) {
   int rad[4];
   const int passes = bfp::pass_count(log2n, plan);
   for (int p = 0; p < 4; ++p) rad[p] = bfp::pass_radix(log2n, plan, p);
-  const bool merged = bfp::merged_twiddles(prec);
+  const bool merged = !products && bfp::merged_twiddles(prec);
   std::vector<std::complex<double>> t = bfp::twiddle_table(log2n, rad, passes, merged);
   if ((int)t.size() != bfp::twiddle_entries(log2n, plan, merged))
     return fail(BFP_EINVAL, "internal: twiddle table size mismatch");
@@ -179,6 +176,8 @@ void free_plan(bfp_plan p) {
   int cur = 0;
   (void)hipGetDevice(&cur);
   (void)hipSetDevice(p->device);
+  if (p->tw32 != p->tw) (void)hipFree(p->tw32);
+  if (p->tw32_alt != p->tw_alt) (void)hipFree(p->tw32_alt);
   (void)hipFree(p->tw);
   (void)hipFree(p->tw_alt);
   (void)hipFree(p->nonfinite);
@@ -186,7 +185,6 @@ void free_plan(bfp_plan p) {
   (void)hipFree(p->items);
   (void)hipFree(p->xform_d);
   (void)hipFree(p->queue);
-  if (p->tw32 != p->tw) (void)hipFree(p->tw32);
   (void)hipFree(p->ent_partial);
   (void)hipFree(p->pg_partial);
   for (void *t : p->tw_sizes) (void)hipFree(t);
@@ -243,7 +241,7 @@ int run_rows(bfp_plan p, int op, const void *in, void *out, const void *filter,
   a.engine = p->tune_engine;
   a.rows_per_thread = p->tune_rr;
   if (p->tune_rr == 2 && p->tune_bpc == kAutoBpc && p->tune_plan == 0 && !ent_partial)
-    a.rows_per_thread = auto_rows_per_thread(p, op, rows, filter != nullptr);
+    a.rows_per_thread = auto_rows_per_thread(p, op, rows, (eff & BFP_FLAG_OUT_FP32) != 0);
   a.ent_partial = ent_partial;
   a.row_exp = row_exp;
   if (row_exp) a.flags |= bfp::KF_ADAPT;
@@ -357,6 +355,13 @@ int fft_plan(bfp_plan *out, int n, int batch, int prec, unsigned flags) {
   if ((flags & BFP_FLAG_AUTOFOCUS) && bfp::second_plan(l)) p->tune_plan = 1;
   st = upload_twiddles(l, prec, 0, &p->tw);
   if (!st && bfp::second_plan(l)) st = upload_twiddles(l, prec, 1, &p->tw_alt);
+  if (prec == BFP_FP32) {
+    p->tw32 = p->tw;
+    p->tw32_alt = p->tw_alt;
+  } else if (flags & BFP_FLAG_AUTOFOCUS) {
+    if (!st) st = upload_twiddles(l, prec, 0, &p->tw32, true);
+    if (!st && bfp::second_plan(l)) st = upload_twiddles(l, prec, 1, &p->tw32_alt, true);
+  }
   if (st) {
     free_plan(p);
     return st;
@@ -379,7 +384,6 @@ int fft_plan(bfp_plan *out, int n, int batch, int prec, unsigned flags) {
     return fail(BFP_ENOMEM, "hipMalloc entropy workspace failed");
   }
   if (flags & BFP_FLAG_AUTOFOCUS) {
-    p->tw32 = p->tw;  // both admitted modes keep FP32 twiddles
     const size_t bytes = sizeof(float) * (size_t)bfp::phase_grad_scratch_floats(l);
     if (hipMalloc((void **)&p->pg_partial, bytes) != hipSuccess) {
       free_plan(p);
@@ -707,7 +711,7 @@ int sar_azimuth_phase_grad(bfp_plan az_plan, const void *rc_t, const void *g, co
   a.filter = h_az;
   a.phasor = az_plan->phasor;
   a.tw32 = az_plan->tw32;
-  a.tw32_alt = az_plan->tw_alt;  // FP32 as well in both admitted modes
+  a.tw32_alt = az_plan->tw32_alt;
   a.partial = az_plan->pg_partial;
   a.grad = grad_phase;
   a.rows = n_range;

@@ -34,10 +34,10 @@ __global__ void __launch_bounds__(256) entropy_partial_kernel(const c32 *__restr
   const long long stride = (long long)gridDim.x * blockDim.x;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride) {
     const c32 v = img[i];
-    // |I|^2 and its logarithm in FP32 (the image is FP32; log2_pos), sums in FP64
+    // |I|^2 and its logarithm in FP32 (the image is FP32; ln_pos), sums in FP64
     const float a = v.x * v.x + v.y * v.y;
     s += a;
-    q += (double)a * (double)log2_pos(a);  // 0 ln 0 = 0: log2_pos(0) is finite
+    q += (double)a * (double)ln_pos(a);  // 0 ln 0 = 0: ln_pos(0) is finite
   }
   sh[0][threadIdx.x] = s;
   sh[1][threadIdx.x] = q;
@@ -51,7 +51,7 @@ __global__ void __launch_bounds__(256) entropy_partial_kernel(const c32 *__restr
   }
   if (threadIdx.x == 0) {
     partial[2 * blockIdx.x] = sh[0][0];
-    partial[2 * blockIdx.x + 1] = sh[1][0] * kLn2;
+    partial[2 * blockIdx.x + 1] = sh[1][0];
   }
 }
 
@@ -140,30 +140,22 @@ hipError_t launch_entropy_noalloc(const void *img, long long count, double *stat
 }
 
 // dE/dI scaled by an upstream factor: G = g (-2/S)(ln|I|^2 - ln S + E) I
-// = (k1 log2|I|^2 + k2) I, with the two factors of an image formed in FP64
-// (no branch: at I = 0 the factor is finite, since log2_pos is, and G = 0)
-struct EntropyGrad {
-  float k1, k2;
-  __device__ __forceinline__ EntropyGrad(double S, double E, float g) {
-    const double f = -2.0 / S * (double)g;
-    k1 = (float)(f * kLn2);
-    k2 = (float)(f * (E - log(S)));
-  }
-  __device__ __forceinline__ c32 operator()(c32 v) const {
-    const float a = v.x * v.x + v.y * v.y;
-    const float c = __builtin_fmaf(k1, log2_pos(a), k2);
-    return c32{c * v.x, c * v.y};
-  }
-};
+// (no branch: at I = 0 the factor is finite, since ln_pos is, and G = 0)
+__device__ __forceinline__ c32 entropy_grad_of(c32 v, double S, double E, float g) {
+  const float a = v.x * v.x + v.y * v.y;
+  const float c = (float)(-2.0 / S) * ((ln_pos(a) - (float)log(S)) + (float)E) * g;
+  return c32{c * v.x, c * v.y};
+}
 
 __global__ void __launch_bounds__(256) entropy_grad_kernel(const c32 *__restrict__ img,
                                                            const double *__restrict__ stats,
                                                            const float *__restrict__ scale,
                                                            c32 *__restrict__ grad, long long count) {
-  const EntropyGrad grad_of(stats[0], stats[2], scale ? scale[0] : 1.0f);
+  const double S = stats[0], E = stats[2];
+  const float g = scale ? scale[0] : 1.0f;
   const long long stride = (long long)gridDim.x * blockDim.x;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride)
-    grad[i] = grad_of(img[i]);
+    grad[i] = entropy_grad_of(img[i], S, E, g);
 }
 
 hipError_t launch_entropy_grad(const void *img, const double *stats, const float *scale, void *grad,
@@ -251,7 +243,11 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) phase_grad_kernel
   const c32 *ph = static_cast<const c32 *>(a.phasor);
   const c32 *gin = static_cast<const c32 *>(a.gimg);
   const StoreT *rc = static_cast<const StoreT *>(a.rc_t);
-  const EntropyGrad grad_of(FUSED ? a.stats[0] : 1.0, FUSED ? a.stats[2] : 0.0, 1.0f);
+  double S = 0.0, Ent = 0.0;
+  if constexpr (FUSED) {
+    S = a.stats[0];
+    Ent = a.stats[2];
+  }
   float acc[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] = 0.0f;
@@ -272,7 +268,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) phase_grad_kernel
         load_row<G>(v[q], gin, row, ti);
         if constexpr (FUSED) {
 #pragma unroll
-          for (int e = 0; e < E; ++e) v[q][e] = grad_of(v[q][e]);
+          for (int e = 0; e < E; ++e) v[q][e] = entropy_grad_of(v[q][e], S, Ent, 1.0f);
         }
       } else {
 #pragma unroll

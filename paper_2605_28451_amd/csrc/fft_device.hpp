@@ -353,36 +353,45 @@ __device__ __forceinline__ void dft(C (&x)[R], Leaf leaf = Leaf{}) {
 }
 
 // ---------------------------------------------- DFTs after products ------
-// Packed FP16 DFTs by radix-4 steps, for the passes whose twiddles are
-// products ahead of the DFT (ModeFP16).  CJ returns the conjugated
-// outputs: the last combining step takes conjugated operands (conj(x + y) =
-// conj x + conj y, conj(-i y) = i conj y), source negations of the packed
-// adds.
+// DFTs by radix-4 steps, for the passes whose twiddles are products ahead of
+// the DFT (kSteps).  CJ returns the conjugated outputs: the last combining
+// step takes conjugated operands (conj(x + y) = conj x + conj y, conj(-i y) =
+// i conj y), source negations of the adds.
 #define BFP_C8 0.70710678118654752440f
 #define BFP_C16 0.92387953251128675613f
 #define BFP_S16 0.38268343236508977173f
 
-__device__ __forceinline__ h2 rot_mi(h2 a) { return h2{a.y, -a.x}; }  // x (-i)
-__device__ __forceinline__ h2 rot_pi(h2 a) { return h2{-a.y, a.x}; }  // x (+i)
+template <class C>
+__device__ __forceinline__ C rot_mi(C a) { return C{a.y, -a.x}; }  // x (-i)
+// x k, and the constant c + i s in the type of a product's operand
+__device__ __forceinline__ c32 times_k(c32 a, float k) {
+  BFP_NO_CONTRACT
+  return c32{a.x * k, a.y * k};
+}
+__device__ __forceinline__ h2 times_k(h2 a, float k) { return a * h2{(f16)k, (f16)k}; }
+__device__ __forceinline__ c32 pair_of(c32, float c, float s) { return c32{c, s}; }
+__device__ __forceinline__ h2 pair_of(h2, float c, float s) { return h2{(f16)c, (f16)s}; }
 
 // a * W_R^e, W_R = exp(-2 pi i / R), e a compile-time constant below R / 2 + 2
-template <int R, int e>
-__device__ __forceinline__ h2 mulw(h2 a) {
-  const h2 k8 = h2{(f16)BFP_C8, (f16)BFP_C8};
+template <int R, int e, class C>
+__device__ __forceinline__ C mulw(C a) {
   if constexpr (e == 0) return a;
   else if constexpr (4 * e == R) return rot_mi(a);
-  else if constexpr (8 * e == R) return (a + rot_mi(a)) * k8;      // e^{-i pi/4}
-  else if constexpr (8 * e == 3 * R) return (rot_mi(a) - a) * k8;  // e^{-3i pi/4}
+  else if constexpr (8 * e == R) return times_k(cadd(a, rot_mi(a)), BFP_C8);      // e^{-i pi/4}
+  else if constexpr (8 * e == 3 * R) return times_k(csub(rot_mi(a), a), BFP_C8);  // e^{-3i pi/4}
   else {
     static_assert(R == 16 && (e == 1 || e == 3 || e == 9), "odd powers of W_16 of a 4 x 4 DFT16");
-    return cmul(a, h2{(f16)(e == 1 ? BFP_C16 : e == 3 ? BFP_S16 : -BFP_C16),
-                      (f16)(e == 1 ? -BFP_S16 : e == 3 ? -BFP_C16 : BFP_S16)});
+    return cmul(a, pair_of(C{}, e == 1 ? BFP_C16 : e == 3 ? BFP_S16 : -BFP_C16,
+                           e == 1 ? -BFP_S16 : e == 3 ? -BFP_C16 : BFP_S16));
   }
 }
 
-template <bool CJ = false>
-__device__ __forceinline__ void dft4(h2 &a, h2 &b, h2 &c, h2 &d) {
-  h2 s0 = cadd(a, c), s1 = csub(a, c), s2 = cadd(b, d), s3 = csub(b, d);
+// (leaf: how a first pass takes its pairs, LeafPlain after products)
+template <bool CJ = false, class C, class Leaf = LeafPlain>
+__device__ __forceinline__ void dft4(C &a, C &b, C &c, C &d, Leaf leaf = Leaf{}) {
+  C s0 = a, s1 = c, s2 = b, s3 = d;
+  bf_leaf(s0, s1, leaf);
+  bf_leaf(s2, s3, leaf);
   if constexpr (CJ) {
     s0 = cconj(s0);
     s1 = cconj(s1);
@@ -401,24 +410,24 @@ __device__ __forceinline__ void dft4(h2 &a, h2 &b, h2 &c, h2 &d) {
 }
 
 // In place, natural order in and out.
-template <int R, bool CJ>
-__device__ __forceinline__ void dft_steps(h2 (&v)[R]) {
+template <int R, bool CJ, class C, class Leaf = LeafPlain>
+__device__ __forceinline__ void dft_steps(C (&v)[R], Leaf leaf = Leaf{}) {
   if constexpr (R == 2) {
     static_assert(!CJ, "conjugates fold into a radix-4 step only");
-    const h2 t = v[0], u = v[1];
+    const C t = v[0], u = v[1];
     v[0] = cadd(t, u);
     v[1] = csub(t, u);
   } else if constexpr (R == 4) {
-    dft4<CJ>(v[0], v[1], v[2], v[3]);
+    dft4<CJ>(v[0], v[1], v[2], v[3], leaf);
   } else if constexpr (R == 8) {
     // n = n2 + 2 n1 (n2 < 2, n1 < 4), k = k1 + 4 k2
     static_assert(!CJ, "conjugates fold into a radix-4 step only");
-    dft4(v[0], v[2], v[4], v[6]);  // n2 = 0 -> slots 0,2,4,6 hold k1 = 0..3
-    dft4(v[1], v[3], v[5], v[7]);  // n2 = 1
+    dft4(v[0], v[2], v[4], v[6], leaf);  // n2 = 0 -> slots 0,2,4,6 hold k1 = 0..3
+    dft4(v[1], v[3], v[5], v[7], leaf);  // n2 = 1
     v[3] = mulw<8, 1>(v[3]);
     v[5] = mulw<8, 2>(v[5]);
     v[7] = mulw<8, 3>(v[7]);
-    h2 y[8];
+    C y[8];
 #pragma unroll
     for (int k1 = 0; k1 < 4; ++k1) {
       y[k1] = cadd(v[2 * k1], v[2 * k1 + 1]);
@@ -431,7 +440,7 @@ __device__ __forceinline__ void dft_steps(h2 (&v)[R]) {
     // n = n2 + 4 n1, k = k1 + 4 k2: DFT4 over n1, twiddle W16^{n2 k1},
     // DFT4 over n2.
 #pragma unroll
-    for (int n2 = 0; n2 < 4; ++n2) dft4(v[n2], v[n2 + 4], v[n2 + 8], v[n2 + 12]);
+    for (int n2 = 0; n2 < 4; ++n2) dft4(v[n2], v[n2 + 4], v[n2 + 8], v[n2 + 12], leaf);
     // slot n2 + 4 k1 now holds Y[n2][k1]
     v[5] = mulw<16, 1>(v[5]);
     v[6] = mulw<16, 2>(v[6]);
@@ -445,7 +454,7 @@ __device__ __forceinline__ void dft_steps(h2 (&v)[R]) {
 #pragma unroll
     for (int k1 = 0; k1 < 4; ++k1) dft4<CJ>(v[4 * k1], v[4 * k1 + 1], v[4 * k1 + 2], v[4 * k1 + 3]);
     // slot k2 + 4 k1 holds X[k1 + 4 k2]: transpose the 4x4 slot grid
-    h2 y[16];
+    C y[16];
 #pragma unroll
     for (int k1 = 0; k1 < 4; ++k1)
 #pragma unroll
@@ -589,13 +598,19 @@ __device__ __forceinline__ void st_row(T *p, T v) {
 //   Comp: register arithmetic type; Tw: twiddle table element;
 //   Filt: filter element;
 //   kMerged: twiddles merged into the butterflies (dft_tw, with kTwice4 as
-//   its TWICE4), or a product per value (twiddle) ahead of dft;
+//   its TWICE4), or a product per value (twiddle) ahead of the DFT, by
+//   dft_steps (kSteps) or dft;
 //   first_leaf(): how a first pass takes values as decoded
 // and the conversions/multiplies the engine needs.
 
+// FP32 throughout, twiddles as products ahead of radix-4 steps: merged into
+// the butterflies they take 5% less arithmetic and half the table reads, but
+// each level rounds its twiddles anew, and results lie up to 6% further from
+// FP64 (64 points 1.04, 512 1.04, 2048 1.02, 4096 1.00 of the error of a
+// forward transform, 1.06, 1.05, 1.02, 0.99 of a compression's).
 struct ModeFP32 {
   typedef c32 Store; typedef c32 Lds; typedef c32 Comp; typedef c32 Tw; typedef c32 Filt;
-  static constexpr bool kMerged = true, kTwice4 = false;
+  static constexpr bool kMerged = false, kTwice4 = false, kSteps = true;
   static __device__ __forceinline__ LeafPlain first_leaf() { return LeafPlain{}; }
   static __device__ __forceinline__ Comp decode(Store s) { return s; }
   static __device__ __forceinline__ Store encode(Comp v) { return v; }
@@ -603,6 +618,7 @@ struct ModeFP32 {
   static __device__ __forceinline__ void store(Store *p, unsigned i, Comp v) { st_stream(p + i, v); }
   static __device__ __forceinline__ Lds to_lds(Comp v) { return v; }
   static __device__ __forceinline__ Comp from_lds(Lds v) { return v; }
+  static __device__ __forceinline__ Comp twiddle(Lds v, Tw w) { return cmul(v, w); }
   static __device__ __forceinline__ Comp fmul(Comp v, Filt h) { return cmul(v, h); }
   static __device__ __forceinline__ Comp round_store(Comp v) { return v; }
 };
@@ -613,7 +629,7 @@ struct ModeFP32 {
 // (16384) and 3.5% (a round trip of 16384) more error on the result.
 struct ModeFP16 {
   typedef h2 Store; typedef h2 Lds; typedef h2 Comp; typedef h2 Tw; typedef h2 Filt;
-  static constexpr bool kMerged = false, kTwice4 = false;
+  static constexpr bool kMerged = false, kTwice4 = false, kSteps = true;
   static __device__ __forceinline__ LeafPlain first_leaf() { return LeafPlain{}; }
   static __device__ __forceinline__ Comp decode(Store s) { return s; }
   static __device__ __forceinline__ Store encode(Comp v) { return v; }
@@ -628,15 +644,14 @@ struct ModeFP16 {
 
 __device__ __forceinline__ c32 h2_to_c32(h2 v) { return c32{(float)v.x, (float)v.y}; }
 
-// Base-2 logarithm of a positive FP32 value: the hardware's (v_log_f32,
-// about 1 ulp) instead of the library's correctly-scaled sequence (about 11
-// instructions more); sums and factors take their ln 2 once, not per value.
-// The hardware instruction does not take denormal inputs, so arguments below
-// the smallest normal number are raised to it: for an image power p that small
+// Natural logarithm of a positive FP32 value from the hardware base-2
+// logarithm (v_log_f32, about 1 ulp) and one multiply, instead of the
+// library's correctly-scaled sequence (about 11 instructions more).  The
+// hardware instruction does not take denormal inputs, so arguments below the
+// smallest normal number are raised to it: for an image power p that small
 // the terms p ln p and p (ln p + c) are below 1e-36.
-constexpr double kLn2 = 0.693147180559945309417;
-__device__ __forceinline__ float log2_pos(float a) {
-  return __builtin_amdgcn_logf(fmaxf(a, 1.17549435e-38f));
+__device__ __forceinline__ float ln_pos(float a) {
+  return __builtin_amdgcn_logf(fmaxf(a, 1.17549435e-38f)) * 0.693147180559945309f;
 }
 // Rounded as a pair (v_cvt_pk_f16_f32).  Two scalar conversions may be folded
 // into the FMAs that made v.x and v.y (v_fma_mixlo/mixhi_f16), in one kernel
@@ -648,7 +663,7 @@ __device__ __forceinline__ h2 c32_to_h2(c32 v) {
 
 struct ModeF16StoreF32 {
   typedef h2 Store; typedef h2 Lds; typedef c32 Comp; typedef c32 Tw; typedef h2 Filt;
-  static constexpr bool kMerged = true, kTwice4 = true;
+  static constexpr bool kMerged = true, kTwice4 = true, kSteps = false;
   static __device__ __forceinline__ LeafScaled first_leaf() { return leaf_one(); }
   static __device__ __forceinline__ Comp decode(Store s) { return h2_to_c32(s); }
   static __device__ __forceinline__ Store encode(Comp v) { return c32_to_h2(v); }
@@ -681,7 +696,7 @@ __device__ __forceinline__ c32 cmul_dot2(h2 a, h2 b) {
 
 struct ModeF16MulF32Acc {
   typedef h2 Store; typedef h2 Lds; typedef c32 Comp; typedef h2 Tw; typedef h2 Filt;
-  static constexpr bool kMerged = false, kTwice4 = false;
+  static constexpr bool kMerged = false, kTwice4 = false, kSteps = false;
   static __device__ __forceinline__ LeafScaled first_leaf() { return leaf_one(); }
   static __device__ __forceinline__ Comp decode(Store s) { return h2_to_c32(s); }
   static __device__ __forceinline__ Store encode(Comp v) { return c32_to_h2(v); }
@@ -694,10 +709,11 @@ struct ModeF16MulF32Acc {
   static __device__ __forceinline__ Comp round_store(Comp v) { return h2_to_c32(c32_to_h2(v)); }
 };
 
+// FP8 storage around the arithmetic of ModeFP32: rows are its results, rounded.
 template <int MANT, int BIAS>
 struct ModeFP8 {
   typedef fp8x2 Store; typedef c32 Lds; typedef c32 Comp; typedef c32 Tw; typedef c32 Filt;
-  static constexpr bool kMerged = true, kTwice4 = false;
+  static constexpr bool kMerged = false, kTwice4 = false, kSteps = true;
   static __device__ __forceinline__ LeafPlain first_leaf() { return LeafPlain{}; }
   typedef Fp8Codec<MANT> Codec;
   static __device__ __forceinline__ Comp decode(Store b) {
@@ -710,6 +726,7 @@ struct ModeFP8 {
   static __device__ __forceinline__ void store(Store *p, unsigned i, Comp v) { st_stream(p + i, encode(v)); }
   static __device__ __forceinline__ Lds to_lds(Comp v) { return v; }
   static __device__ __forceinline__ Comp from_lds(Lds v) { return v; }
+  static __device__ __forceinline__ Comp twiddle(Lds v, Tw w) { return cmul(v, w); }
   static __device__ __forceinline__ Comp fmul(Comp v, Filt h) { return cmul(v, h); }
   static __device__ __forceinline__ Comp round_store(Comp v) { return decode(encode(v)); }
 };

@@ -221,7 +221,7 @@ struct Engine {
   // after a radix-2 or radix-8 step form (dft_steps), whose last additions the
   // compiler may contract with products differently once signs sit in between:
   // there the conjugate follows the transform and every kernel rounds alike.
-  static constexpr bool kSteps = !M::kMerged && std::is_same<Comp, h2>::value;
+  static constexpr bool kSteps = M::kSteps;
   static constexpr int kLastRadix = G::radix(G::S::P - 1);
   static constexpr bool kFoldConj = !kSteps || kLastRadix == 4 || kLastRadix == 16;
   // Twiddle rows of a pass held by a thread: one per butterfly.
@@ -270,7 +270,8 @@ struct Engine {
       Comp u[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) u[r] = v[b + B * r];
-      if constexpr (kSteps) dft_steps<R, cj>(u);
+      if constexpr (kSteps && PASS == 0) dft_steps<R, cj>(u, leaf);
+      else if constexpr (kSteps) dft_steps<R, cj>(u);
       else if constexpr (PASS > 0 && M::kMerged) dft_tw<R, cj, M::kTwice4>(u, w + b * (R / 2));
       else if constexpr (PASS > 0) dft<R, cj>(u);
       else dft<R, cj>(u, leaf);

@@ -60,8 +60,8 @@ hipError_t launch_rows(int mode, int log2n, int op, bool out32, const RowArgs &a
 // (plan: 0 or 1, the radix plans of fft_engine.hpp; merged: the layout of the
 // arithmetic whose butterflies carry the twiddles)
 int twiddle_entries(int log2n, int plan, bool merged);
-// the modes' kMerged: all but pure FP16 and FP16-multiply
-inline bool merged_twiddles(int mode) { return mode != 1 && mode != 3; }
+// the modes' kMerged: FP16 storage with FP32 arithmetic
+inline bool merged_twiddles(int mode) { return mode == 2; }
 int pass_count(int log2n, int plan = 0);
 int pass_radix(int log2n, int plan, int p);
 bool second_plan(int log2n);
@@ -116,8 +116,8 @@ struct PhaseGradArgs {
   const void *rc_t;      // range-compressed data, plan storage (FP16 or FP32)
   const void *filter;    // azimuth filter, plan filter format
   const void *phasor;    // FP32 pairs exp(i phi_m)
-  const void *tw32;      // FP32 twiddle table of the size (radix plan 0)
-  const void *tw32_alt;  // FP32 twiddle table of radix plan 1 (sizes with two plans)
+  const void *tw32;      // FP32 product table of the size (radix plan 0)
+  const void *tw32_alt;  // that of radix plan 1 (sizes with two plans)
   float *partial;        // kPhaseGradBlocks * transforms-per-workgroup rows of n floats
   float *grad;           // n floats out
   int rows;

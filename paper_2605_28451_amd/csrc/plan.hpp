@@ -15,6 +15,9 @@ struct bfp_plan_s {
   int device = 0;
   void *tw = nullptr;                         // rows: this size's table
   void *tw_alt = nullptr;                     // rows: the second radix plan's table
+  // autofocus plans: the phase gradient's FP32 tables, twiddles as products
+  // (in FP32 plans tw and tw_alt themselves)
+  void *tw32 = nullptr, *tw32_alt = nullptr;
   unsigned long long *nonfinite = nullptr;    // device counter
   void *phasor = nullptr;                     // n FP32 pairs (rows plans)
   int phasor_sign = 0;  // what the last call left in phasor: 0 nothing, +1 exp(+i phi)
@@ -36,7 +39,6 @@ struct bfp_plan_s {
   int cu_count = 0;
   int uneven_max_bpc = 1;
   // autofocus workspace
-  void *tw32 = nullptr;          // FP32 twiddles (owned only when tw is FP16)
   double *ent_partial = nullptr; // kEntropyBlocks x 2 doubles
   float *pg_partial = nullptr;   // phase-gradient partial rows
   void *tw_sizes[7] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};

@@ -140,7 +140,7 @@ __device__ __forceinline__ int xcd_group(int it, int groups) {
 }
 
 // The image entropy sums of a workgroup: a fixed-order tree of the threads'
-// (S, Q / ln 2) in `sh` (2 * WG doubles of LDS, free once the caller's barrier has
+// (S, Q) in `sh` (2 * WG doubles of LDS, free once the caller's barrier has
 // passed), written as the workgroup's partial; a second kernel adds the
 // partials.  (Finishing the total in the workgroup that arrives last would
 // need a device-scope release per workgroup, an L2 writeback in the middle
@@ -159,7 +159,7 @@ __device__ __forceinline__ void entropy_sums(const RowArgs &a, double es, double
   }
   if (threadIdx.x == 0) {
     a.ent_partial[2 * blockIdx.x] = sh[0];
-    a.ent_partial[2 * blockIdx.x + 1] = sh[WG] * kLn2;
+    a.ent_partial[2 * blockIdx.x + 1] = sh[WG];
   }
 }
 
@@ -453,7 +453,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N>::WG), (row_waves<M, LOG2N, OP
           const c32 z = to_c32(v[e]);
           const float p = z.x * z.x + z.y * z.y;
           es += p;
-          eq += (double)p * (double)log2_pos(p);  // 0 ln 0 = 0: log2_pos(0) is finite
+          eq += (double)p * (double)ln_pos(p);  // 0 ln 0 = 0: ln_pos(0) is finite
         }
       }
     } else {
@@ -649,7 +649,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
               const c32 z = to_c32(v[q][e]);
               const float p = z.x * z.x + z.y * z.y;
               es += p;
-              eq += (double)p * (double)log2_pos(p);
+              eq += (double)p * (double)ln_pos(p);
             }
           }
         } else {

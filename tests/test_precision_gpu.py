@@ -9,9 +9,11 @@ may exceed the emulation's by the spread of an RMS over M independent values,
 """
 import numpy as np
 import pytest
+import torch
 
 import oracle
-from paper_2605_28451_amd import api, scenes
+from paper_2605_28451_amd import _lib, api, scenes
+from paper_2605_28451_amd.autofocus import AutofocusPlan
 from tests.gpu_util import announce, download, need_gpu, rand_rows, upload
 
 pytestmark = pytest.mark.gpu
@@ -47,7 +49,10 @@ class Pair:
 
         def fma(a, b, c):
             return (a.astype(np.float64) * b.astype(np.float64) + c.astype(np.float64)).astype(dt)
-        return Pair(fma(self.re, wr, -(self.im * wi)), fma(self.im, wr, self.re * wi))
+        re = fma(self.re, wr, -(self.im * wi))
+        if dt == np.float16:  # packed: the swizzled operand's product first
+            return Pair(re, fma(self.im, wr, self.re * wi))
+        return Pair(re, fma(self.re, wi, self.im * wr))
 
     def value(self):
         return self.re.astype(np.float64) + 1j * self.im.astype(np.float64)
@@ -128,3 +133,52 @@ def test_fp16_forward_error(n):
     x = scenes.quantize(rand_rows(rows, n, n), "fp16")
     got = download(api.FFTPlan(n, rows, "fp16").forward(upload(x, "fp16")), "fp16")
     check(got, oracle.fft(x), product_form(x, RADICES[n], np.float16), f"fp16.n{n}")
+
+
+@pytest.mark.parametrize("n", sorted(RADICES))
+def test_fp32_forward_error(n):
+    need_gpu()
+    rows = VALUES // n
+    announce(f"fp32 forward error {rows}x{n}")
+    x = scenes.quantize(rand_rows(rows, n, n), "fp32")
+    got = download(api.FFTPlan(n, rows, "fp32").forward(upload(x, "fp32")), "fp32")
+    check(got, oracle.fft(x), product_form(x, RADICES[n], np.float32), f"fp32.n{n}")
+
+
+@pytest.mark.parametrize("n", [64, 512, 2048])
+@pytest.mark.parametrize("mode", ["e4m3", "e5m2"])
+def test_fp8_forward_to_fp32_error(mode, n):
+    # FP8 inputs, FP32 outputs: no rounding to FP8 hides that of the transform
+    need_gpu()
+    rows = VALUES // n
+    announce(f"{mode} forward to fp32 error {rows}x{n}")
+    x = scenes.quantize(rand_rows(rows, n, n, 0.125), mode)
+    plan = api.FFTPlan(n, rows, mode, flags=_lib.FLAG_OUT_FP32)
+    got = download(plan.forward(upload(x, mode)), "fp32")
+    check(got, oracle.fft(x), product_form(x, RADICES[n], np.float32), f"{mode}_to_fp32.n{n}")
+
+
+@pytest.mark.parametrize("mode", ["fp32", "fp16_fp32"])
+@pytest.mark.parametrize("n,radix_plan", [(512, 0), (512, 1), (1024, 0), (1024, 1)])
+def test_phase_gradient_error(mode, n, radix_plan):
+    # the gradient's FP32 transforms, row by row (one row: no sum over rows);
+    # phase 0, so that grad = Im(IDFT(DFT(g) conj H) conj x)
+    need_gpu()
+    announce(f"phase gradient error {mode} n={n} radix plan {radix_plan}")
+    fmt, radices = api.storage_format(mode), (RADICES1 if radix_plan else RADICES)[n]
+    rows = VALUES // n
+    g = scenes.quantize(rand_rows(rows, n, n), "fp32")
+    x = scenes.quantize(rand_rows(rows, n, n + 1), fmt)
+    h = np.exp(2j * np.pi * np.random.default_rng(n).random(n))
+    hq = scenes.quantize(oracle.matched_filter(np.fft.ifft(np.conj(h)), n), api.filter_format(mode))
+    plan = AutofocusPlan(n, 1, mode)
+    plan.set_tuning_ex(1, -1, 2, radix_plan)
+    filt = api.filter_tensor(np.fft.ifft(np.conj(h)), n, mode)
+    gd, xd, phase = upload(g, "fp32"), upload(x, fmt), torch.zeros(n, device="cuda")
+    got = torch.stack([plan.phase_grad(xd[r:r + 1], gd[r:r + 1], filt, phase) for r in range(rows)])
+    ref = np.imag(oracle.fft(oracle.fft(g) * np.conj(hq), inverse=True) * np.conj(x))
+    z = _pair(product_form(g, radices, np.float32), np.float32).times(hq.real, -hq.imag)
+    back = Pair(z.re / np.float32(n), -z.im / np.float32(n)).value()
+    v = np.conj(product_form(back, radices, np.float32))
+    emulated = (v.imag * x.real - (v.real * x.imag).astype(np.float32)).astype(np.float32)
+    check(got.cpu().numpy().astype(np.float64), ref, emulated.astype(np.float64), f"phase_grad.{mode}.n{n}.{radix_plan}")
