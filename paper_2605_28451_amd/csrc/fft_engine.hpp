@@ -309,15 +309,8 @@ struct Engine {
       for (int e = 0; e < E; ++e) raw[e] = lds[lds_slot<In, T>(tp, e)];
       gather<PASS>(v, raw, w);
     }
-    // Large FP16-multiply transforms load the next rows after the butterflies:
-    // 32 FP32 values beside both row sets would not fit 64 registers.
-    constexpr bool kLate = !M::kMerged && !kSteps && T >= 1024;
-    if constexpr (!kLate) load_tw<PASS + 1>(tw, t, wn);
+    load_tw<PASS + 1>(tw, t, wn);
     butterflies<PASS, CJ>(v, w, leaf);
-    if constexpr (kLate) {
-      asm volatile("" : "+v"(t));
-      load_tw<PASS + 1>(tw, t, wn);
-    }
     if constexpr (!LAST) {
       typedef Pad<LOG2N, PASS, PLAN> Out;
       static_assert(pad_splits<Out, G::N, R, NS>(), "padded offsets of a butterfly must not straddle a pad");

@@ -173,15 +173,6 @@ __device__ __forceinline__ void entropy_sums(const RowArgs &a, double es, double
 template <int OP, int T, class X>
 constexpr bool keep_output = OP != OP_INV && T * sizeof(X) >= 64;
 
-// Wavefronts per SIMD to compile for (0: no constraint).  The forward
-// transform of 16384 points with FP16 on chip fits two 1024-thread workgroups
-// per CU if it keeps to 64 registers; with FP32 arithmetic (the FP16-multiply
-// mode) it took 72, 155 us for 4096 rows against 121 us at 64.
-template <class M, int LOG2N, int OP>
-constexpr int row_waves() {
-  return Geometry<LOG2N>::WG == 1024 && OP == OP_FWD && sizeof(typename M::Lds) == 4 ? 8 : 0;
-}
-
 // PIPE (persistent grids, where the engine keeps its twiddles in registers):
 // the twiddle rows are loaded once per workgroup, and the next row group's
 // data is loaded into registers while the current group is transformed, so
@@ -190,7 +181,7 @@ constexpr int row_waves() {
 // of the caches faster (pure FP16, 2048 x 4096: 15.7 against 16.4 us with
 // nontemporal loads; the kernels that do not prefetch gain nothing from it).
 template <class M, int LOG2N, int OP, int V, bool OUT32, bool PIPE>
-__global__ void __launch_bounds__((Geometry<LOG2N>::WG), (row_waves<M, LOG2N, OP>())) row_kernel(RowArgs a) {
+__global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
   typedef Geometry<LOG2N> G;
   typedef Engine<M, LOG2N> EN;
   typedef typename M::Comp Comp;
@@ -799,6 +790,7 @@ static hipError_t launch_mfma(const RowArgs &a, hipStream_t s) {
 template <int LOG2N, int OP, int V, bool OUT32>
 static hipError_t launch_vector(const RowArgs &a, hipStream_t s) {
   typedef Geometry<LOG2N> G;
+  typedef KernelMode<MODE, LOG2N, OP == OP_FWD> M;
   unsigned grid = (unsigned)((a.rows + G::TPW - 1) / G::TPW);
   if (a.grid_limit > 0 && grid > (unsigned)a.grid_limit) grid = (unsigned)a.grid_limit;
   if (a.grid_out) *a.grid_out = (int)grid;
@@ -818,7 +810,7 @@ static hipError_t launch_vector(const RowArgs &a, hipStream_t s) {
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((row_kernel<MODE, LOG2N, OP, V, OUT32, false>), dim3(grid), dim3(G::WG), 0, s, a);
+  hipLaunchKernelGGL((row_kernel<M, LOG2N, OP, V, OUT32, false>), dim3(grid), dim3(G::WG), 0, s, a);
   return hipGetLastError();
 }
 
@@ -827,6 +819,7 @@ static hipError_t launch_vector(const RowArgs &a, hipStream_t s) {
 template <int LOG2N, int OP, int V, bool OUT32>
 static bool launch_rr(const RowArgs &a, hipStream_t s, hipError_t &err) {
   typedef Geometry<LOG2N> G;
+  typedef KernelMode<MODE, LOG2N, OP == OP_FWD> M;
   if constexpr ((V & ~(V_CONJ | V_PHASOR | V_ENT)) != 0 || ((V & V_PHASOR) && OP != OP_COMPRESS)) {
     return false;
   } else {
@@ -849,9 +842,9 @@ static bool launch_rr(const RowArgs &a, hipStream_t s, hipError_t &err) {
       constexpr bool kPipe = Engine<MODE, LOG2N>::kTwRegs && NB == 2;
       if (a.grid_out) *a.grid_out = (int)grid;
       if (kPipe && a.grid_limit > 0)
-        hipLaunchKernelGGL((row_kernel_rr<MODE, LOG2N, OP, V, OUT32, RR, 2, kPipe>), dim3(grid), dim3(G::WG), 0, s, a);
+        hipLaunchKernelGGL((row_kernel_rr<M, LOG2N, OP, V, OUT32, RR, 2, kPipe>), dim3(grid), dim3(G::WG), 0, s, a);
       else
-        hipLaunchKernelGGL((row_kernel_rr<MODE, LOG2N, OP, V, OUT32, RR, NB, false>), dim3(grid), dim3(G::WG), 0, s, a);
+        hipLaunchKernelGGL((row_kernel_rr<M, LOG2N, OP, V, OUT32, RR, NB, false>), dim3(grid), dim3(G::WG), 0, s, a);
       err = hipGetLastError();
       return true;
     }
@@ -872,6 +865,7 @@ static bool launch_plan1(const RowArgs &a, hipStream_t s, hipError_t &err) {
     return false;
   } else {
     typedef Geometry<LOG2N, 1> G;
+    typedef KernelMode<MODE, LOG2N, OP == OP_FWD> M;
     constexpr long kRow = (long)G::TPW * G::LDS_N * sizeof(typename MODE::Lds);
     if (a.radix_plan != 1 || !a.tw_alt) return false;
     RowArgs b = a;
@@ -882,7 +876,7 @@ static bool launch_plan1(const RowArgs &a, hipStream_t s, hipError_t &err) {
       unsigned grid = (unsigned)((a.rows + G::TPW * RR - 1) / (G::TPW * RR));
       if (a.grid_limit > 0 && grid > (unsigned)a.grid_limit) grid = (unsigned)a.grid_limit;
       if (a.grid_out) *a.grid_out = (int)grid;
-      hipLaunchKernelGGL((row_kernel_rr<MODE, LOG2N, OP, V, OUT32, RR, NB, false, 1>), dim3(grid),
+      hipLaunchKernelGGL((row_kernel_rr<M, LOG2N, OP, V, OUT32, RR, NB, false, 1>), dim3(grid),
                          dim3(G::WG), 0, s, b);
       err = hipGetLastError();
     };

@@ -52,9 +52,10 @@ constexpr int UNEVEN_LDS = 16384 + 16384 / 16;  // largest per-item LDS (element
 // OFF32: the packed batch spans less than 4 GiB, so every access is a
 // uniform base plus a 32-bit byte offset (one 32-bit add per access instead
 // of a 64-bit address per lane).
-template <class M, int LOG2N, bool INV, bool OFF32>
-__device__ __forceinline__ void uneven_item(const UnevenArgs &a, int4 d, typename M::Lds *lds_all,
+template <class MODE0, int LOG2N, bool INV, bool OFF32>
+__device__ __forceinline__ void uneven_item(const UnevenArgs &a, int4 d, typename MODE0::Lds *lds_all,
                                             int tid) {
+  typedef KernelMode<MODE0, LOG2N, !INV> M;  // the bits of the row kernels
   typedef Geometry<LOG2N> G;
   typedef Engine<M, LOG2N> EN;
   typedef typename M::Comp Comp;
