@@ -146,3 +146,41 @@ def test_uneven_empty_and_single():
     assert sqnr_db(oracle.fft(x[None])[0], y) >= 56.0
     with pytest.raises(api._lib.BfpError):
         api.UnevenPlan([7], [0], "fp16")
+
+
+@pytest.mark.parametrize("mode", ["fp32", "fp16", "fp16_fp32", "fp16_mul_fp32_acc", "e4m3"])
+@pytest.mark.parametrize("over", [0, 1, None])
+def test_uneven_tiles_per_cu(mode, over):
+    # both sides of the default's line, 4 tiles per CU (16384 points: a tile
+    # each) and one more, and a mixed batch far beyond it: one workgroup per
+    # tile, the queue on the smallest grid and the default's own launch give
+    # the bits of the per-size row launches
+    need_gpu()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(3)
+    if over is None:
+        log2n = rng.integers(8, 15, 20000).astype(np.int32)
+    else:
+        log2n = np.full(4 * cus + over, 14, np.int32)
+    inv = rng.integers(0, 2, log2n.size).astype(np.uint8)
+    announce(f"uneven tiles per CU {mode} {log2n.size} transforms")
+    fmt = api.storage_format(mode)
+    plan = api.UnevenPlan(log2n, inv, mode)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn((plan.total, 2), generator=g, device="cuda").mul_(0.125)
+    xd = api.convert(x, "fp32", fmt) if fmt != "fp32" else x
+    y = plan.execute(xd).clone()
+    for bpc in (1, 64):
+        plan.set_tuning(0, bpc)
+        assert torch.equal(plan.execute(xd), y), bpc
+    offsets = torch.from_numpy(np.ascontiguousarray(plan.offsets[:log2n.size])).cuda()
+    for e in range(8, 15):
+        for d in (0, 1):
+            idx = np.nonzero((log2n == e) & (inv == d))[0]
+            if idx.size == 0:
+                continue
+            at = (offsets[torch.from_numpy(idx).cuda()][:, None] + torch.arange(1 << e, device="cuda")[None, :]).reshape(-1)
+            p = api.FFTPlan(1 << e, idx.size, mode)
+            rows = xd[at].reshape(idx.size, 1 << e, 2)
+            r = p.inverse_bfp(rows) if d else p.forward(rows)
+            assert torch.equal(y[at], r.reshape(-1, 2)), (e, d)
