@@ -60,43 +60,66 @@ enum Variant { V_PLAIN = 0, V_NAIVE = 1, V_CONJ = 2, V_PHASOR = 4, V_TRANS = 8, 
 // signed bin (k - N for k >= N/2), which is the band-limited (periodic sinc)
 // interpolation moving the compressed row s_r bins toward smaller range.
 // A thread's bins are k' = t + T e (e < E/2) and t + T e - N (e >= E/2), so
-// its phasors are base . step^e (times a wrap phasor for the upper half),
-// sincospif of phases reduced to [-1/2, 1/2] cycles and FP32 complex products
-// (at most 8 in a row: their error stays below 1e-6); the product with H is
-// formed in FP32 and rounded once to the filter type.
+// its phasors are base . step^e (times a wrap phasor for the upper half).
+// step, step^2, step^4 and wrap are each a sincospif of their own phase,
+// reduced to [-1/2, 1/2] cycles (shift . 2^j / E is exact), so a phasor is at
+// most 6 FP32 products of factors rounded once (0.8e-7 rms; the powers of step
+// taken by squaring put 2.3e-7 on it, one recurrence over e 2.0e-7); the
+// product with H is formed in FP32 and rounded once to the filter type.
 //
-// The phases are formed while the row's loads are in flight (taken after the
+// The sines are formed while the row's loads are in flight (taken after the
 // forward transform, the shift's load and the sines added their latency to
-// every row), step and wrap by one sincospif in pairs of lanes of one
-// transform, and the powers of step run as four chains instead of one.
+// every row), one for each lane of a quad of lanes of one transform, and
+// handed round where they are used: 4 registers wait for the transform.
 __device__ __forceinline__ c32 cycles_phasor(float cyc) {
   cyc -= rintf(cyc);
   float sn, cs;
   sincospif(2.0f * cyc, &sn, &cs);
   return c32{cs, sn};
 }
-// the value of the even (ODD = false) or odd lane of each pair, in both
-template <bool ODD>
-__device__ __forceinline__ float of_pair(float v) {
-  constexpr int quad = ODD ? 0xF5 : 0xA0;  // lanes (1, 1, 3, 3) or (0, 0, 2, 2)
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), quad, 0xf, 0xf, true));
+// the value of lane Q of each quad, in all four
+template <int Q>
+__device__ __forceinline__ c32 of_quad(c32 v) {
+  auto get = [](float f) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, f), Q * 0x55, 0xf, 0xf, true));
+  };
+  return c32{get(v.x), get(v.y)};
 }
 struct Ramp {
-  c32 base, step, wrap;
+  c32 base, own;  // own: the lane's factor of the quad's (T >= 4)
+  float sr;
 };
+// step^1, step^2, step^4, and up = step^4 wrap, which enters the upper half
+struct RampSteps {
+  c32 step, step2, step4, up;
+};
+// shift times this is the phase of factor Q in cycles: step^(2^Q), and wrap, or
+// with E = 8 values per thread (where step^4 serves in up alone) up
+template <int E, int Q>
+constexpr float ramp_turn() { return Q < 3 ? (float)(1 << Q) / E : E == 8 ? -0.5f : -1.0f; }
 template <int N, int T>
 __device__ __forceinline__ Ramp ramp_phasors(unsigned t, float sr) {
-  Ramp r;
-  r.base = cycles_phasor((float)t * sr * (1.0f / N));
-  if constexpr (T >= 2) {
-    const c32 w = cycles_phasor((threadIdx.x & 1) ? -sr : sr * ((float)T / N));
-    r.step = c32{of_pair<false>(w.x), of_pair<false>(w.y)};
-    r.wrap = c32{of_pair<true>(w.x), of_pair<true>(w.y)};
-  } else {
-    r.step = cycles_phasor(sr * ((float)T / N));
-    r.wrap = cycles_phasor(-sr);
-  }
+  constexpr int E = N / T;
+  Ramp r = {cycles_phasor((float)t * sr * (1.0f / N)), c32{}, sr};
+  const int q = threadIdx.x & 3;
+  if constexpr (T >= 4)
+    r.own = cycles_phasor(sr * (q == 0 ? ramp_turn<E, 0>() : q == 1 ? ramp_turn<E, 1>()
+                                : q == 2 ? ramp_turn<E, 2>() : ramp_turn<E, 3>()));
   return r;
+}
+template <int N, int T, int Q>
+__device__ __forceinline__ c32 ramp_factor(const Ramp &r) {
+  if constexpr (T >= 4) return of_quad<Q>(r.own);
+  else return cycles_phasor(r.sr * ramp_turn<N / T, Q>());
+}
+template <int N, int T>
+__device__ __forceinline__ RampSteps ramp_steps(const Ramp &r) {
+  RampSteps s = {ramp_factor<N, T, 0>(r), ramp_factor<N, T, 1>(r), c32{}, ramp_factor<N, T, 3>(r)};
+  if constexpr (N / T > 8) {
+    s.step4 = ramp_factor<N, T, 2>(r);
+    s.up = cmul(s.step4, s.up);
+  }
+  return s;
 }
 __device__ __forceinline__ void filt_from_c32(c32 v, c32 &h) { h = v; }
 __device__ __forceinline__ void filt_from_c32(c32 v, h2 &h) { h = c32_to_h2(v); }
@@ -173,6 +196,14 @@ __device__ __forceinline__ void entropy_sums(const RowArgs &a, double es, double
 template <int OP, int T, class X>
 constexpr bool keep_output = OP != OP_INV && T * sizeof(X) >= 64;
 
+// Wavefronts per SIMD to compile for (0: no constraint).  The pure-FP16 ramp
+// kernel of 8192 points takes 69 registers without, 63 (no scratch) with: 4
+// instead of 3 workgroups per CU, 41 against 43 us for 16M points.
+template <class M, int LOG2N, int V>
+constexpr int row_waves() {
+  return std::is_same<M, ModeFP16>::value && LOG2N == 13 && V == V_RAMP ? 8 : 0;
+}
+
 // PIPE (persistent grids, where the engine keeps its twiddles in registers):
 // the twiddle rows are loaded once per workgroup, and the next row group's
 // data is loaded into registers while the current group is transformed, so
@@ -181,7 +212,7 @@ constexpr bool keep_output = OP != OP_INV && T * sizeof(X) >= 64;
 // of the caches faster (pure FP16, 2048 x 4096: 15.7 against 16.4 us with
 // nontemporal loads; the kernels that do not prefetch gain nothing from it).
 template <class M, int LOG2N, int OP, int V, bool OUT32, bool PIPE>
-__global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
+__global__ void __launch_bounds__((Geometry<LOG2N>::WG), (row_waves<M, LOG2N, V>())) row_kernel(RowArgs a) {
   typedef Geometry<LOG2N> G;
   typedef Engine<M, LOG2N> EN;
   typedef typename M::Comp Comp;
@@ -378,10 +409,9 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
       for (int e = 0; e < E; ++e) v[e] = conj_scale(v[e], sc);
     } else if constexpr (ramp) {
       static_assert(E % 8 == 0, "four chains, the upper half on whole groups");
-      const c32 step2 = cmul(rp.step, rp.step), step4 = cmul(step2, step2);
-      const c32 up = cmul(step4, rp.wrap);  // into the upper half
-      c32 r[4] = {rp.base, cmul(rp.base, rp.step), cmul(rp.base, step2), {}};
-      r[3] = cmul(r[1], step2);
+      const RampSteps st = ramp_steps<N, T>(rp);
+      c32 r[4] = {rp.base, cmul(rp.base, st.step), cmul(rp.base, st.step2), {}};
+      r[3] = cmul(r[1], st.step2);
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         Filt h;
@@ -389,7 +419,7 @@ __global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
         else h = f[tt + T * e];
         filt_from_c32(cmul(to_c32(h), r[e & 3]), h);
         v[e] = fold_in<K, E>(M::fmul(v[e], h), e);
-        if (e + 4 < E) r[e & 3] = cmul(r[e & 3], (e & ~3) + 4 == E / 2 ? up : step4);
+        if (e + 4 < E) r[e & 3] = cmul(r[e & 3], (e & ~3) + 4 == E / 2 ? st.up : st.step4);
       }
     } else if (OP == OP_COMPRESS || f) {
 #pragma unroll

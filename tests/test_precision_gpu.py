@@ -182,3 +182,27 @@ def test_phase_gradient_error(mode, n, radix_plan):
     v = np.conj(product_form(back, radices, np.float32))
     emulated = (v.imag * x.real - (v.real * x.imag).astype(np.float32)).astype(np.float32)
     check(got.cpu().numpy().astype(np.float64), ref, emulated.astype(np.float64), f"phase_grad.{mode}.n{n}.{radix_plan}")
+
+
+@pytest.mark.parametrize("n", [8, 32, 64, 512, 2048, 16384])
+def test_migration_ramp_error(n):
+    # range_compress_rcmc against the plain compression of the same rows: what
+    # the ramp adds.  A factor (a sine and a cosine to one unit in the last
+    # place, uniform) is off by d = 2^-24 sqrt(2/3) = 4.9e-8 rms.  base, wrap
+    # (half the bins), step and step^2 (half each) and step^4 k times (k = 0 ..
+    # 3, k^2 = 3.5 on average) make sqrt(1 + 0.5 + 1 + 3.5) d = 1.2e-7, four
+    # rounded products 2 . 4e-8 more: 1.45e-7 together.
+    need_gpu()
+    rows = VALUES // n
+    announce(f"migration ramp error {rows}x{n}")
+    rng = np.random.default_rng(n)
+    x = scenes.quantize(rand_rows(rows, n, n), "fp32")
+    replica = np.fft.ifft(np.exp(2j * np.pi * rng.random(n)))
+    hq = scenes.quantize(oracle.matched_filter(replica, n), "fp32")
+    shift = rng.uniform(-12.0, 12.0, rows).astype(np.float32)
+    plan, filt, xd = api.FFTPlan(n, rows, "fp32"), api.filter_tensor(replica, n, "fp32"), upload(x, "fp32")
+    ref0, ref = oracle.compress(x, hq), oracle.rcmc_compress(x, hq, shift.astype(np.float64))
+    plain = rms(download(plan.range_compress(xd, filt), "fp32") - ref0) / rms(ref0)
+    ramp = rms(download(plan.range_compress_rcmc(xd, filt, torch.from_numpy(shift).cuda()), "fp32") - ref) / rms(ref)
+    print(f"[measure] precision.rcmc.n{n} plain {plain:.3e} with the ramp {ramp:.3e}")
+    assert ramp <= np.hypot(plain, 1.45e-7)
