@@ -585,10 +585,13 @@ __device__ __forceinline__ void st_kept_g(global_ptr<T> p, T v) {
     __scoped_atomic_store_n(reinterpret_cast<global_ptr<unsigned long long>>(p),
                             __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED, __MEMORY_SCOPE_DEVICE);
 }
-// KEEP: st_kept_g, else nontemporal
-template <bool KEEP, class T>
+// How a row output is stored: nontemporal, through to the last-level cache
+// (st_kept_g), or plainly
+enum RowStore { ROW_STREAMED, ROW_KEPT, ROW_CACHED };
+template <RowStore HOW, class T>
 __device__ __forceinline__ void st_row(T *p, T v) {
-  if constexpr (KEEP) st_kept_g((global_ptr<T>)p, v);
+  if constexpr (HOW == ROW_KEPT) st_kept_g((global_ptr<T>)p, v);
+  else if constexpr (HOW == ROW_CACHED) *p = v;
   else st_stream(p, v);
 }
 

@@ -173,7 +173,7 @@ constexpr bool pad_splits() {
 // base in scalar registers and the immediates 0, T, 2T, 3T elements, so all
 // sixteen accesses share one 32-bit lane offset (ti, which must be < T).
 // STREAM: nontemporal (row data read once); otherwise cached (tables every
-// row reads, such as a filter or a phasor: row = 0).  KEEP: see st_kept_g.
+// row reads, such as a filter or a phasor: row = 0).  HOW: see RowStore.
 // (The pipelined row kernel keeps per-lane pointers: there the compiler
 // turns this form into 64-bit address arithmetic per store.)
 template <class G, bool STREAM = true, class X>
@@ -192,7 +192,7 @@ __device__ __forceinline__ void load_row(X (&x)[G::E], const void *base, long lo
     }
   }
 }
-template <class G, bool KEEP, class X>
+template <class G, RowStore HOW, class X>
 __device__ __forceinline__ void store_row(void *base, long long row, unsigned ti, const X (&x)[G::E]) {
   static_assert(G::E % 4 == 0, "elements go in groups of four");
   X *dst = static_cast<X *>(base) + row * G::N;
@@ -203,7 +203,8 @@ __device__ __forceinline__ void store_row(void *base, long long row, unsigned ti
     const global_ptr<X> g = (global_ptr<X>)grp;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      if constexpr (KEEP) st_kept_g(g + (ti + (unsigned)(G::T * k)), x[e + k]);
+      if constexpr (HOW == ROW_KEPT) st_kept_g(g + (ti + (unsigned)(G::T * k)), x[e + k]);
+      else if constexpr (HOW == ROW_CACHED) grp[ti + (unsigned)(G::T * k)] = x[e + k];
       else st_stream_g(g + (ti + (unsigned)(G::T * k)), x[e + k]);
     }
   }

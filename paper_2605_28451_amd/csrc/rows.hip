@@ -186,15 +186,25 @@ __device__ __forceinline__ void entropy_sums(const RowArgs &a, double es, double
   }
 }
 
-// Whether a row output of type X is stored so that the next call finds it in
-// the last-level cache (st_kept_g): every operation but the inverse, where the
-// T threads of a transform write at least 64 consecutive bytes per
-// instruction.  Below that the write-through sends each line on in several
-// parts: 16-point forward transforms of 200000 rows (FP16) took 47 us so
-// against 11 us with nontemporal stores, 128-point ones of 40000 rows (32
-// bytes) 16.7 against 12.3 us.
-template <int OP, int T, class X>
-constexpr bool keep_output = OP != OP_INV && T * sizeof(X) >= 64;
+// How the T threads of an N-point transform store a row of type X:
+//  - a thread that holds a whole row of 64 bytes or more, plainly: L2 gathers the
+//    parts of its lines, which nontemporal stores send on one by one, in a time
+//    that depends on the order they are issued in (16-point compressions of 1M
+//    rows, FP16 with FP32 output: 181 or 298 us by the kernel's order, 61
+//    plainly; FP16 output 47 and 38; shorter rows and T = 2 .. 8 are 2 to 5%
+//    faster nontemporally);
+//  - below 64 consecutive bytes per instruction (T sizeof(X)) nontemporally:
+//    write-through stores send each line on in several parts (16-point forward
+//    transforms of 200000 rows, FP16: 47 against 11 us, 128-point ones of 40000
+//    rows 16.7 against 12.3 us);
+//  - otherwise so that the next call finds the row in the last-level cache
+//    (st_kept_g), but nontemporally for the inverse.  FP32 frames of 4096 x 4096
+//    and 2048 x 4096: 186.9 against 195.4 and 96.0 against 104.8 us; a lone
+//    compression whose own inputs lie in that cache takes up to 5% more (102
+//    against 105 us for 2048 rows of 8192).
+template <int OP, int N, int T, class X>
+constexpr RowStore row_store = T == 1 && N * sizeof(X) >= 64 ? ROW_CACHED
+                               : T * sizeof(X) < 64 || OP == OP_INV ? ROW_STREAMED : ROW_KEPT;
 
 // Wavefronts per SIMD to compile for (0: no constraint).  The pure-FP16 ramp
 // kernel of 8192 points takes 69 registers without, 63 (no scratch) with: 4
@@ -328,7 +338,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N>::WG), (row_waves<M, LOG2N, V>
   }
   // (and in the FP32-arithmetic modes converted, or as two product operands:
   // 32 registers instead of 16)
-  if constexpr (kHoist) {
+  if constexpr (kHoist && (PIPE || sizeof(Comp) == 8)) {
 #pragma unroll
     for (int e = 0; e < E; ++e) asm volatile("" : "+v"(hf[e]));
   }
@@ -461,12 +471,12 @@ __global__ void __launch_bounds__((Geometry<LOG2N>::WG), (row_waves<M, LOG2N, V>
       if constexpr (PIPE) {
         c32 *dst = static_cast<c32 *>(a.out) + row * N + tt;
 #pragma unroll
-        for (int e = 0; e < E; ++e) st_row<keep_output<OP, T, c32>>(dst + (unsigned)(T * e), to_c32(v[e]));
+        for (int e = 0; e < E; ++e) st_row<row_store<OP, N, T, c32>>(dst + (unsigned)(T * e), to_c32(v[e]));
       } else {
         c32 o[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) o[e] = to_c32(v[e]);
-        store_row<G, keep_output<OP, T, c32>>(a.out, row, tt & (T - 1), o);
+        store_row<G, row_store<OP, N, T, c32>>(a.out, row, tt & (T - 1), o);
       }
       if constexpr (ent) {
 #pragma unroll
@@ -481,12 +491,12 @@ __global__ void __launch_bounds__((Geometry<LOG2N>::WG), (row_waves<M, LOG2N, V>
       if constexpr (!kRowIo) {
         Store *dst = static_cast<Store *>(a.out) + row * N + tt;
 #pragma unroll
-        for (int e = 0; e < E; ++e) st_row<keep_output<OP, T, Store>>(dst + (unsigned)(T * e), M::encode(v[e]));
+        for (int e = 0; e < E; ++e) st_row<row_store<OP, N, T, Store>>(dst + (unsigned)(T * e), M::encode(v[e]));
       } else {
         Store o[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) o[e] = M::encode(v[e]);
-        store_row<G, keep_output<OP, T, Store>>(a.out, row, tt & (T - 1), o);
+        store_row<G, row_store<OP, N, T, Store>>(a.out, row, tt & (T - 1), o);
       }
     }
     if (a.flags & KF_CHECK_FINITE) {
@@ -662,7 +672,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
         if constexpr (OUT32) {
           c32 *dst = static_cast<c32 *>(a.out) + row * N + tt;
 #pragma unroll
-          for (int e = 0; e < E; ++e) st_row<keep_output<OP, T, c32>>(dst + (unsigned)(T * e), to_c32(v[q][e]));
+          for (int e = 0; e < E; ++e) st_row<row_store<OP, N, T, c32>>(dst + (unsigned)(T * e), to_c32(v[q][e]));
           if constexpr (ent) {
             // as in row_kernel: |I|^2 and |I|^2 ln |I|^2 in FP32, sums in FP64
 #pragma unroll
@@ -676,7 +686,7 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) row_kernel_rr(Row
         } else {
           Store *dst = static_cast<Store *>(a.out) + row * N + tt;
 #pragma unroll
-          for (int e = 0; e < E; ++e) st_row<keep_output<OP, T, Store>>(dst + (unsigned)(T * e), M::encode(v[q][e]));
+          for (int e = 0; e < E; ++e) st_row<row_store<OP, N, T, Store>>(dst + (unsigned)(T * e), M::encode(v[q][e]));
         }
         if (a.flags & KF_CHECK_FINITE) {
 #pragma unroll

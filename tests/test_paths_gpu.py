@@ -345,3 +345,25 @@ def test_fp8_storage_kernels_round_the_fp32_path(mode):
         diff = np.array(mism / (2.0 * v32.size))
         measure(f"fp8_bits_mismatch_fraction.{mode}.{name}", float(diff.mean()))
         assert diff.mean() < 1e-4, name
+
+
+@pytest.mark.parametrize("mode", ["fp32", "fp16", "fp16_fp32", "fp16_mul_fp32_acc", "e4m3"])
+@pytest.mark.parametrize("n", [8, 16, 32])
+def test_short_rows_storage_and_fp32_outputs_agree(mode, n):
+    # rows of a whole thread (8 and 16 points) are stored plainly from 64 bytes
+    # on, shorter ones and parts of rows nontemporally: the FP32 output rounded
+    # to the storage format is the storage output, and nothing beyond the last
+    # (ragged) row is written
+    need_gpu()
+    rows, fmt = 1027, api.storage_format(mode)
+    announce(f"short rows {mode} {rows}x{n}")
+    x = upload(scenes.quantize(scenes.gaussian_rows(n, rows, n) * 0.25, fmt), fmt)
+    H = api.filter_tensor(scenes.range_replica_padded(n, n // 2), n, mode)
+    plan = api.FFTPlan(n, rows, mode)
+    wide = torch.full((rows + 1, n, 2), 7.0, device="cuda")
+    buf = torch.full((rows + 1, n, 2), 7, dtype=api.TORCH_DTYPE[fmt], device="cuda")
+    plan.range_compress(x, H, out=wide[:rows], out_fp32=True)
+    plan.range_compress(x, H, out=buf[:rows])
+    want = wide[:rows].clone() if fmt == "fp32" else api.convert(wide[:rows].contiguous(), "fp32", fmt)
+    assert torch.equal(buf[:rows], want)
+    assert bool((wide[rows:] == 7.0).all()) and bool((buf[rows:] == 7).all())
