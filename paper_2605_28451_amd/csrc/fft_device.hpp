@@ -33,7 +33,6 @@ struct __attribute__((aligned(8))) c32 {
 // (one row or two rows per thread, a fused or a separate pass) could round
 // differently.  Written out, every kernel gets the same bits.
 #define BFP_NO_CONTRACT _Pragma("clang fp contract(off)")
-__device__ __forceinline__ c32 mk(float x, float y) { return c32{x, y}; }
 __device__ __forceinline__ c32 cadd(c32 a, c32 b) { return c32{a.x + b.x, a.y + b.y}; }
 __device__ __forceinline__ c32 csub(c32 a, c32 b) { return c32{a.x - b.x, a.y - b.y}; }
 // a - i b and a + i b
@@ -108,14 +107,13 @@ __device__ __forceinline__ h2 conj_pow2(h2 a) {
 // (a, b) -> (a + w b, a - w b), every operation an explicit FMA (contraction
 // off), so every kernel gets the same bits.  NEGI takes -i w for w (a swap of
 // components and a sign, free as operand selects), CJ returns the conjugated
-// results (signs only).  The forms differ in how w is given:
+// results (signs only).  The forms differ in how w is given (the FMA butterfly
+// of Linzer and Feig, 1993):
 //   bf_one   w = 1 (or -i): additions;
 //   bf_tan   w = g (1 + i t), |t| <= 1 (COS), or w = g (t + i) (!COS):
-//            u = b + t (i b) (or t b + i b), then a +- g u: 6 FMAs on FP32
-//            pairs and 3 on packed FP16, against 8 and 4 for a product and
-//            two sums, with one rounding less;
-//   bf_fma   w = (re, im): a +- w b, 8 (4) FMAs;
-//   bf_twice w = (re, im): s = a + w b, then 2 a - s: 6 (3), one rounding
+//            u = b + t (i b) (or t b + i b), then a +- g u: 6 FMAs, against
+//            8 operations for a product and two sums, with one rounding less;
+//   bf_twice w = (re, im): s = a + w b, then 2 a - s: 6 FMAs, one rounding
 //            more on the difference.
 template <bool NEGI, bool CJ, class C>
 __device__ __forceinline__ void bf_one(C &a, C &b) {
@@ -142,64 +140,26 @@ __device__ __forceinline__ void bf_scaled(c32 &a, c32 &b, c32 u, float g) {
   a = p;
   b = q;
 }
-template <bool NEGI, bool CJ>
-__device__ __forceinline__ void bf_scaled(h2 &a, h2 &b, h2 u, f16 g) {
-  BFP_NO_CONTRACT
-  const h2 r = NEGI ? h2{u.y, -u.x} : u, gg = h2{g, g};
-  const h2 c = CJ ? cconj(a) : a, v = CJ ? cconj(r) : r;
-  a = __builtin_elementwise_fma(v, gg, c);
-  b = __builtin_elementwise_fma(-v, gg, c);
-}
-
 template <bool COS>
 __device__ __forceinline__ c32 bf_turn(c32 b, float t) {
   BFP_NO_CONTRACT
   if constexpr (COS) return c32{__builtin_fmaf(-b.y, t, b.x), __builtin_fmaf(b.x, t, b.y)};
   else return c32{__builtin_fmaf(b.x, t, -b.y), __builtin_fmaf(b.y, t, b.x)};
 }
-template <bool COS>
-__device__ __forceinline__ h2 bf_turn(h2 b, f16 t) {
-  BFP_NO_CONTRACT
-  if constexpr (COS) return __builtin_elementwise_fma(h2{-b.y, b.x}, h2{t, t}, b);
-  else return __builtin_elementwise_fma(b, h2{t, t}, h2{-b.y, b.x});
-}
-template <bool COS, bool NEGI, bool CJ, class C, class W>
-__device__ __forceinline__ void bf_tan(C &a, C &b, W w) {  // w = (g, t)
+template <bool COS, bool NEGI, bool CJ>
+__device__ __forceinline__ void bf_tan(c32 &a, c32 &b, c32 w) {  // w = (g, t)
   bf_scaled<NEGI, CJ>(a, b, bf_turn<COS>(b, w.y), w.x);
 }
 
 template <bool NEGI, bool CJ>
-__device__ __forceinline__ void bf_fma(c32 &a, c32 &b, c32 w) {
+__device__ __forceinline__ void bf_twice(c32 &a, c32 &b, c32 w) {
   BFP_NO_CONTRACT
+  const c32 c = CJ ? cconj(a) : a;
   const float wx = NEGI ? w.y : w.x, wy = NEGI ? -w.x : w.y;
-  const float px = __builtin_fmaf(wx, b.x, __builtin_fmaf(-wy, b.y, a.x));
-  const float qx = __builtin_fmaf(-wx, b.x, __builtin_fmaf(wy, b.y, a.x));
   const float sg = CJ ? -1.0f : 1.0f;  // folds into the operands' signs
-  const float py = __builtin_fmaf(sg * wx, b.y, __builtin_fmaf(sg * wy, b.x, sg * a.y));
-  const float qy = __builtin_fmaf(-(sg * wx), b.y, __builtin_fmaf(-(sg * wy), b.x, sg * a.y));
-  a = c32{px, py};
-  b = c32{qx, qy};
-}
-template <bool NEGI, bool CJ>
-__device__ __forceinline__ void bf_fma(h2 &a, h2 &b, h2 w) {
-  BFP_NO_CONTRACT
-  const h2 r = NEGI ? h2{b.y, -b.x} : b;
-  const h2 m = CJ ? h2{-r.y, -r.x} : h2{-r.y, r.x};  // i r, conjugated if CJ
-  const h2 n = CJ ? cconj(r) : r, c = CJ ? cconj(a) : a;
-  const h2 wx = h2{w.x, w.x}, wy = h2{w.y, w.y};
-  a = __builtin_elementwise_fma(n, wx, __builtin_elementwise_fma(m, wy, c));
-  b = __builtin_elementwise_fma(-n, wx, __builtin_elementwise_fma(-m, wy, c));
-}
-
-template <bool NEGI, bool CJ, class C, class W>
-__device__ __forceinline__ void bf_twice(C &a, C &b, W w) {
-  BFP_NO_CONTRACT
-  const C c = CJ ? cconj(a) : a;
-  C p = a, q = b;
-  bf_fma<NEGI, CJ>(p, q, w);  // the difference of this form is not used
-  a = p;
-  if constexpr (sizeof(C) == 8) b = C{__builtin_fmaf(2.0f, c.x, -p.x), __builtin_fmaf(2.0f, c.y, -p.y)};
-  else b = __builtin_elementwise_fma(c, C{(f16)2.0f, (f16)2.0f}, -p);
+  a = c32{__builtin_fmaf(wx, b.x, __builtin_fmaf(-wy, b.y, a.x)),
+          __builtin_fmaf(sg * wx, b.y, __builtin_fmaf(sg * wy, b.x, sg * a.y))};
+  b = c32{__builtin_fmaf(2.0f, c.x, -a.x), __builtin_fmaf(2.0f, c.y, -a.y)};
 }
 
 // ------------------------------------------------------------ DFTs ------
@@ -213,39 +173,34 @@ __device__ __forceinline__ void bf_twice(C &a, C &b, W w) {
 // take R - 1.  The angle of omega W_R^k lies in (-2 pi (k + 1) / R,
 // -2 pi k / R]: from R = 8 on each k < R/4 is on one side of -pi/4 for every
 // m, and the tangent form is chosen at compile time.  At R = 4 the angle of
-// omega spans (-pi/2, 0] and at R = 2 (-pi, 0]: those take (re, im), level 4
-// as bf_fma (bf_twice with TWICE4) and level 2 as bf_twice.  A radix-16 pass
-// takes 208 FP32 operations on 16 values (192 with TWICE4; 220 with 15
-// products and a 4 x 4 DFT16) or 104 packed FP16 ones (110), and half the
-// table reads.  Error against FP64 on N(0, 1) input relative to the products,
-// 4096 points: 1.00 in FP32 and FP16 (1.02 with TWICE4, which serves the mode
-// whose error is the FP16 rounding of its exchanges); 0.99 to 1.04 at other
-// sizes and radices.
+// omega spans (-pi/2, 0] and at R = 2 (-pi, 0]: those take (re, im), as
+// bf_twice.  A radix-16 pass takes 192 operations on 16 values (220 with 15
+// products and a 4 x 4 DFT16) and half the table reads.  It rounds each
+// level's twiddles anew: 2 to 5% more FP32 error than products, so it serves
+// the mode whose error is the FP16 rounding of its exchanges, 2000 times
+// larger.
 template <int R>
 constexpr int tw_level() { return R >= 4 ? R / 4 : 1; }  // those of level R
 
-template <int R, bool CJ, bool TWICE4, class C, class W>
-__device__ __forceinline__ void dft_tw(C (&x)[R], const W *w) {
+template <int R, bool CJ>
+__device__ __forceinline__ void dft_tw(c32 (&x)[R], const c32 *w) {
   if constexpr (R == 2) {
     bf_twice<false, CJ>(x[0], x[1], w[0]);
   } else {
-    C e[R / 2], o[R / 2];
+    c32 e[R / 2], o[R / 2];
 #pragma unroll
     for (int k = 0; k < R / 2; ++k) {
       e[k] = x[2 * k];
       o[k] = x[2 * k + 1];
     }
-    dft_tw<R / 2, false, TWICE4>(e, w + tw_level<R>());
-    dft_tw<R / 2, false, TWICE4>(o, w + tw_level<R>());
+    dft_tw<R / 2, false>(e, w + tw_level<R>());
+    dft_tw<R / 2, false>(o, w + tw_level<R>());
 #pragma unroll
     for (int k = 0; k < R / 4; ++k) {
       const int k2 = k + R / 4;
-      if constexpr (R == 4 && TWICE4) {
+      if constexpr (R == 4) {
         bf_twice<false, CJ>(e[k], o[k], w[k]);
         bf_twice<true, CJ>(e[k2], o[k2], w[k]);
-      } else if constexpr (R == 4) {
-        bf_fma<false, CJ>(e[k], o[k], w[k]);
-        bf_fma<true, CJ>(e[k2], o[k2], w[k]);
       } else if (k < R / 8) {
         bf_tan<true, false, CJ>(e[k], o[k], w[k]);
         bf_tan<true, true, CJ>(e[k2], o[k2], w[k]);
@@ -262,13 +217,9 @@ __device__ __forceinline__ void dft_tw(C (&x)[R], const W *w) {
   }
 }
 
-// tan and cos of pi e / 16 (e = 1, 2, 3, 4), to 20 significant digits
-constexpr float kTan16[5] = {0.0f, 0.19891236737965800691f, 0.41421356237309504880f,
-                             0.66817863791929891999f, 1.0f};
-constexpr float kCos16[5] = {1.0f, 0.98078528040323044913f, 0.92387953251128675613f,
-                             0.83146961230254523708f, 0.70710678118654752440f};
-__device__ __forceinline__ c32 tan_pair(c32, float g, float t) { return c32{g, t}; }
-__device__ __forceinline__ h2 tan_pair(h2, float g, float t) { return h2{(f16)g, (f16)t}; }
+// tan and cos of pi e / 8 (e = 1, 2), to 20 significant digits
+constexpr float kTan8[3] = {0.0f, 0.41421356237309504880f, 1.0f};
+constexpr float kCos8[3] = {1.0f, 0.92387953251128675613f, 0.70710678118654752440f};
 
 // How the first level of a first pass takes its pairs (x_r, x_{r + R/2}):
 //   LeafPlain   a + b, a - b;
@@ -314,14 +265,14 @@ __device__ __forceinline__ void bf_leaf(c32 &a, c32 &b, LeafScaled l) {
 
 // The same with omega = 1 (the first pass, and transforms in one pass):
 // W_R^k = cos a - i sin a, a = 2 pi k / R, are constants.
-template <int R, bool CJ = false, class C, class Leaf = LeafPlain>
-__device__ __forceinline__ void dft(C (&x)[R], Leaf leaf = Leaf{}) {
-  static_assert(R == 2 || R == 4 || R == 8 || R == 16 || R == 32, "radix");
+template <int R, bool CJ = false, class Leaf = LeafPlain>
+__device__ __forceinline__ void dft(c32 (&x)[R], Leaf leaf = Leaf{}) {
+  static_assert(R == 2 || R == 4 || R == 8 || R == 16, "radix");
   if constexpr (R == 2) {
     if constexpr (CJ) bf_one<false, true>(x[0], x[1]);  // a last pass of radix 2
     else bf_leaf(x[0], x[1], leaf);
   } else {
-    C e[R / 2], o[R / 2];
+    c32 e[R / 2], o[R / 2];
 #pragma unroll
     for (int k = 0; k < R / 2; ++k) {
       e[k] = x[2 * k];
@@ -333,13 +284,13 @@ __device__ __forceinline__ void dft(C (&x)[R], Leaf leaf = Leaf{}) {
     bf_one<true, CJ>(e[R / 4], o[R / 4]);
 #pragma unroll
     for (int k = 1; k < R / 4; ++k) {
-      const int k2 = k + R / 4, s = 32 / R * k;  // a = pi s / 16
-      if (s <= 4) {  // cos a (1 - i tan a)
-        const C w = tan_pair(C{}, kCos16[s], -kTan16[s]);
+      const int k2 = k + R / 4, s = 16 / R * k;  // a = pi s / 8
+      if (s <= 2) {  // cos a (1 - i tan a)
+        const c32 w = c32{kCos8[s], -kTan8[s]};
         bf_tan<true, false, CJ>(e[k], o[k], w);
         bf_tan<true, true, CJ>(e[k2], o[k2], w);
       } else {       // -sin a (-cot a + i), with sin a = cos(pi/2 - a)
-        const C w = tan_pair(C{}, -kCos16[8 - s], -kTan16[8 - s]);
+        const c32 w = c32{-kCos8[4 - s], -kTan8[4 - s]};
         bf_tan<false, false, CJ>(e[k], o[k], w);
         bf_tan<false, true, CJ>(e[k2], o[k2], w);
       }
@@ -600,9 +551,8 @@ __device__ __forceinline__ void st_row(T *p, T v) {
 //   Store: HBM element; Lds: on-chip element between passes;
 //   Comp: register arithmetic type; Tw: twiddle table element;
 //   Filt: filter element;
-//   kMerged: twiddles merged into the butterflies (dft_tw, with kTwice4 as
-//   its TWICE4), or a product per value (twiddle) ahead of the DFT, by
-//   dft_steps (kSteps) or dft;
+//   kMerged: twiddles merged into the butterflies (dft_tw), or a product per
+//   value (twiddle) ahead of the DFT, by dft_steps (kSteps) or dft;
 //   first_leaf(): how a first pass takes values as decoded
 // and the conversions/multiplies the engine needs.
 
@@ -613,7 +563,7 @@ __device__ __forceinline__ void st_row(T *p, T v) {
 // forward transform, 1.06, 1.05, 1.02, 0.99 of a compression's).
 struct ModeFP32 {
   typedef c32 Store; typedef c32 Lds; typedef c32 Comp; typedef c32 Tw; typedef c32 Filt;
-  static constexpr bool kMerged = false, kTwice4 = false, kSteps = true;
+  static constexpr bool kMerged = false, kSteps = true;
   static __device__ __forceinline__ LeafPlain first_leaf() { return LeafPlain{}; }
   static __device__ __forceinline__ Comp decode(Store s) { return s; }
   static __device__ __forceinline__ Store encode(Comp v) { return v; }
@@ -632,7 +582,7 @@ struct ModeFP32 {
 // (16384) and 3.5% (a round trip of 16384) more error on the result.
 struct ModeFP16 {
   typedef h2 Store; typedef h2 Lds; typedef h2 Comp; typedef h2 Tw; typedef h2 Filt;
-  static constexpr bool kMerged = false, kTwice4 = false, kSteps = true;
+  static constexpr bool kMerged = false, kSteps = true;
   static __device__ __forceinline__ LeafPlain first_leaf() { return LeafPlain{}; }
   static __device__ __forceinline__ Comp decode(Store s) { return s; }
   static __device__ __forceinline__ Store encode(Comp v) { return v; }
@@ -666,7 +616,7 @@ __device__ __forceinline__ h2 c32_to_h2(c32 v) {
 
 struct ModeF16StoreF32 {
   typedef h2 Store; typedef h2 Lds; typedef c32 Comp; typedef c32 Tw; typedef h2 Filt;
-  static constexpr bool kMerged = true, kTwice4 = true, kSteps = false;
+  static constexpr bool kMerged = true, kSteps = false;
   static __device__ __forceinline__ LeafScaled first_leaf() { return leaf_one(); }
   static __device__ __forceinline__ Comp decode(Store s) { return h2_to_c32(s); }
   static __device__ __forceinline__ Store encode(Comp v) { return c32_to_h2(v); }
@@ -686,8 +636,9 @@ struct ModeF16StoreF32 {
 };
 
 // FP16 operands, FP32 accumulation: a b as (a.x, a.y) . (b.x, -b.y) and
-// (a.x, a.y) . (b.y, b.x) with v_dot2_f32_f16, for which the compiler folds no
-// operand selects: the second operands are one flip of the high sign and one
+// (a.x, a.y) . (b.y, b.x) with v_dot2_f32_f16.  The instruction has no operand
+// selects, and its sign modifiers are folded by the compiler only for both
+// halves at once: the second operands are one flip of the high sign and one
 // rotation (a table of both operands doubles its reads, which cost more than
 // the two instructions: 37 against 27 us for the 2048 x 4096 compression).
 __device__ __forceinline__ c32 cmul_dot2(h2 a, h2 b) {
@@ -699,7 +650,7 @@ __device__ __forceinline__ c32 cmul_dot2(h2 a, h2 b) {
 
 struct ModeF16MulF32Acc {
   typedef h2 Store; typedef h2 Lds; typedef c32 Comp; typedef h2 Tw; typedef h2 Filt;
-  static constexpr bool kMerged = false, kTwice4 = false, kSteps = false;
+  static constexpr bool kMerged = false, kSteps = false;
   static __device__ __forceinline__ LeafScaled first_leaf() { return leaf_one(); }
   static __device__ __forceinline__ Comp decode(Store s) { return h2_to_c32(s); }
   static __device__ __forceinline__ Store encode(Comp v) { return c32_to_h2(v); }
@@ -726,7 +677,7 @@ struct ModeF16MulSteps : ModeF16MulF32Acc {
 template <int MANT, int BIAS>
 struct ModeFP8 {
   typedef fp8x2 Store; typedef c32 Lds; typedef c32 Comp; typedef c32 Tw; typedef c32 Filt;
-  static constexpr bool kMerged = false, kTwice4 = false, kSteps = true;
+  static constexpr bool kMerged = false, kSteps = true;
   static __device__ __forceinline__ LeafPlain first_leaf() { return LeafPlain{}; }
   typedef Fp8Codec<MANT> Codec;
   static __device__ __forceinline__ Comp decode(Store b) {

@@ -273,7 +273,7 @@ struct Engine {
       for (int r = 0; r < R; ++r) u[r] = v[b + B * r];
       if constexpr (kSteps && PASS == 0) dft_steps<R, cj>(u, leaf);
       else if constexpr (kSteps) dft_steps<R, cj>(u);
-      else if constexpr (PASS > 0 && M::kMerged) dft_tw<R, cj, M::kTwice4>(u, w + b * (R / 2));
+      else if constexpr (PASS > 0 && M::kMerged) dft_tw<R, cj>(u, w + b * (R / 2));
       else if constexpr (PASS > 0) dft<R, cj>(u);
       else dft<R, cj>(u, leaf);
 #pragma unroll
