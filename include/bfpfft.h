@@ -188,9 +188,10 @@ int fft_plan_get_tuning(bfp_plan p, int *engine, int *blocks_per_cu);
  * together, sharing twiddles and one barrier per LDS exchange; the other
  * variants, the matrix-core engine and sizes whose two rows would not leave
  * LDS for two workgroups per CU (FP32 exchanges above 4096 points, FP16
- * above 8192) ignore it, and with automatic blocks_per_cu and radix_plan 0
- * the library runs one row where that is faster.  For one radix plan, results are the same bits for
- * every engine-independent setting (blocks_per_cu, rows_per_thread).
+ * above 8192) ignore it.  Until this call sets it, a plan whose default is 2
+ * runs one row where that is faster (automatic blocks_per_cu, radix_plan 0).
+ * For one radix plan, results are the same bits for every engine-independent
+ * setting (blocks_per_cu, rows_per_thread).
  * Uneven plans take rows_per_thread = 1 and radix_plan = 0.  A new plan has
  * {1, -1, 2, 0} in the modes with FP32 arithmetic (BFP_FP32,
  * BFP_FP16_STORE_FP32_COMPUTE and the FP8-storage modes) and {1, -1, 1, 0}

@@ -55,8 +55,8 @@ int default_rows_per_thread(int prec) {
   return (prec == BFP_FP16 || prec == BFP_FP16_MUL_FP32_ACC) ? 1 : 2;
 }
 
-// rows_per_thread = 2 under automatic blocks_per_cu and radix plan 0: whether
-// an operation runs two rows per thread.  Two rows share twiddles and
+// The default rows_per_thread = 2 (never set by a call; automatic blocks_per_cu,
+// radix plan 0): whether an operation runs two rows per thread.  Two rows share twiddles and
 // barriers, one row doubles the workgroups and halves their registers and LDS.
 // With g one-row workgroups per CU (figures one row / two rows, us):
 //  - FP32 and FP8, n >= 256: one row up to g = 2 (FP32 compressions of 64, 256
@@ -240,7 +240,7 @@ int run_rows(bfp_plan p, int op, const void *in, void *out, const void *filter,
   a.grid_limit = bpc > 0 ? bpc * p->cu_count : 0;
   a.engine = p->tune_engine;
   a.rows_per_thread = p->tune_rr;
-  if (p->tune_rr == 2 && p->tune_bpc == kAutoBpc && p->tune_plan == 0 && !ent_partial)
+  if (p->rr_default && p->tune_rr == 2 && p->tune_bpc == kAutoBpc && p->tune_plan == 0 && !ent_partial)
     a.rows_per_thread = auto_rows_per_thread(p, op, rows, (eff & BFP_FLAG_OUT_FP32) != 0);
   a.ent_partial = ent_partial;
   a.row_exp = row_exp;
@@ -350,6 +350,7 @@ int fft_plan(bfp_plan *out, int n, int batch, int prec, unsigned flags) {
   p->tune_engine = 1;
   p->tune_bpc = kAutoBpc;
   p->tune_rr = default_rows_per_thread(prec);
+  p->rr_default = true;
   // autofocus plans: the second radix plan, whose phase gradient runs twice
   // the wavefronts per row in the same LDS (82 against 98 us at 4096 x 4096)
   if ((flags & BFP_FLAG_AUTOFOCUS) && bfp::second_plan(l)) p->tune_plan = 1;
@@ -747,6 +748,7 @@ int fft_plan_set_tuning_ex(bfp_plan p, const bfp_tuning *t) {
   int st = fft_plan_set_tuning(p, t->engine, t->blocks_per_cu);
   if (st) return st;
   p->tune_rr = t->rows_per_thread;
+  p->rr_default = false;
   p->tune_plan = t->radix_plan;
   return BFP_OK;
 }

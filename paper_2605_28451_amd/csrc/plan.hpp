@@ -35,6 +35,7 @@ struct bfp_plan_s {
   int tune_engine = 1;     // 0: matrix cores where available, 1: vector ALU (default)
   int tune_bpc = 0;        // workgroups per CU of a persistent grid, 0 = default
   int tune_rr = 1;         // rows per thread (1, or 2: the multi-row kernel)
+  bool rr_default = false; // rows plans: tune_rr is still the default (up to 2, by rule)
   int tune_plan = 0;       // radix plan (0, or 1 where the size has a second)
   int cu_count = 0;
   int uneven_max_bpc = 1;

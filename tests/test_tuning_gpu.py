@@ -256,3 +256,34 @@ def test_automatic_rows_per_thread_bits(mode, n):
             for rr in (1, 2):
                 plan.set_tuning_ex(1, 0, rr, 0)
                 assert torch.equal(run(plan), want), (op, rows, rr)
+
+
+def kernels_of(call):
+    """Names of the kernels that `call` launches."""
+    from torch.profiler import ProfilerActivity, profile
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    names = [e.name for e in prof.events() if "row_kernel" in e.name or "uneven" in e.name]
+    assert names, "no kernel recorded"
+    return names
+
+
+def test_explicit_rows_per_thread_is_kept():
+    # a rows_per_thread that was set, also one beside automatic blocks_per_cu
+    # (as a stored tuning may hold), is what runs, on both sides of the line
+    # that the default draws (2 one-row workgroups per CU)
+    need_gpu()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for rows, default in ((cus, 1), (4 * cus, 2)):
+        announce(f"explicit rows per thread fp32 {rows}x4096")
+        x = torch.zeros((rows, 4096, 2), device="cuda")
+        plan = api.FFTPlan(4096, rows, "fp32")
+        two_rows = [any("row_kernel_rr" in k for k in kernels_of(lambda: plan.forward(x)))]
+        for rr in (1, 2):
+            plan.set_tuning_ex(1, -1, rr, 0)
+            assert plan.get_tuning_ex() == (1, -1, rr, 0)
+            two_rows.append(any("row_kernel_rr" in k for k in kernels_of(lambda: plan.forward(x))))
+        assert two_rows == [default == 2, False, True], (rows, two_rows)
