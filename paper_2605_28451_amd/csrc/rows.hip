@@ -206,14 +206,6 @@ template <int OP, int N, int T, class X>
 constexpr RowStore row_store = T == 1 && N * sizeof(X) >= 64 ? ROW_CACHED
                                : T * sizeof(X) < 64 || OP == OP_INV ? ROW_STREAMED : ROW_KEPT;
 
-// Wavefronts per SIMD to compile for (0: no constraint).  The pure-FP16 ramp
-// kernel of 8192 points takes 69 registers without, 63 (no scratch) with: 4
-// instead of 3 workgroups per CU, 41 against 43 us for 16M points.
-template <class M, int LOG2N, int V>
-constexpr int row_waves() {
-  return std::is_same<M, ModeFP16>::value && LOG2N == 13 && V == V_RAMP ? 8 : 0;
-}
-
 // PIPE (persistent grids, where the engine keeps its twiddles in registers):
 // the twiddle rows are loaded once per workgroup, and the next row group's
 // data is loaded into registers while the current group is transformed, so
@@ -222,7 +214,7 @@ constexpr int row_waves() {
 // of the caches faster (pure FP16, 2048 x 4096: 15.7 against 16.4 us with
 // nontemporal loads; the kernels that do not prefetch gain nothing from it).
 template <class M, int LOG2N, int OP, int V, bool OUT32, bool PIPE>
-__global__ void __launch_bounds__((Geometry<LOG2N>::WG), (row_waves<M, LOG2N, V>())) row_kernel(RowArgs a) {
+__global__ void __launch_bounds__(Geometry<LOG2N>::WG) row_kernel(RowArgs a) {
   typedef Geometry<LOG2N> G;
   typedef Engine<M, LOG2N> EN;
   typedef typename M::Comp Comp;
