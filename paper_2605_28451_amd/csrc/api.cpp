@@ -66,9 +66,11 @@ int default_rows_per_thread(int prec) {
 //    / 18.8): the reads of the twiddle table, one pair of floats per value,
 //    bind the one-row kernel.  (At g = 3 and, for single transforms, from g =
 //    16 on the two lie within 8% either way.)
-//  - FP8, n < 256: one row (E4M3 compression of 65536 x 128 27.3 / 32.8, of
-//    131072 x 64 33.2 / 34.5), but two with FP32 outputs from g = 2 on (40.8 /
-//    34.4 for 131072 x 64).  FP32, n < 256: two.
+//  - FP8, 32 <= n < 256: one row (E4M3 compression of 65536 x 128 27.3 / 32.8,
+//    of 131072 x 64 33.2 / 34.5), but two with FP32 outputs from g = 2 on (40.8
+//    / 34.4 for 131072 x 64); n = 8 and 16: two from g = 8 on (1M rows of 16:
+//    forward 20.9 / 18.5, compression with a phase 27.1 / 26.0, without 22.4 /
+//    23.0; 393216 rows 7.8 / 8.8, 13.1 / 13.0, 10.3 / 10.3).  FP32, n < 256: two.
 //  - FP16 storage, n >= 256 (half the table, merged into the butterflies): one
 //    row (compression of 64, 512, 2048 rows of 4096: 6.4 / 9.5, 9.0 / 10.5,
 //    22.5 / 25.1), but two for the plain forward transform from g = 8 on (n =
@@ -76,10 +78,11 @@ int default_rows_per_thread(int prec) {
 int auto_rows_per_thread(const bfp_plan_s *p, int op, int rows, bool out32) {
   const bool fp16 = p->prec == BFP_FP16_STORE_FP32_COMPUTE, fp32 = p->prec == BFP_FP32;
   if (p->log2n < 8 && (fp16 || fp32)) return 2;
-  if (p->log2n < 8 && !out32) return 1;
+  if (p->log2n >= 5 && p->log2n < 8 && !out32) return 1;
   const int t = bfp::threads_per_transform(p->log2n), per_wg = t < 256 ? 256 / t : 1;
   const long long groups = ((long long)rows + per_wg - 1) / per_wg, cus = p->cu_count;
   if (fp16) return (op == bfp::OP_FWD && groups >= 8 * cus && p->log2n > 8 && p->log2n <= 12) ? 2 : 1;
+  if (p->log2n < 5 && !out32) return groups < 8 * cus ? 1 : 2;
   return groups <= 2 * cus ? 1 : 2;
 }
 

@@ -287,3 +287,21 @@ def test_explicit_rows_per_thread_is_kept():
             assert plan.get_tuning_ex() == (1, -1, rr, 0)
             two_rows.append(any("row_kernel_rr" in k for k in kernels_of(lambda: plan.forward(x))))
         assert two_rows == [default == 2, False, True], (rows, two_rows)
+
+
+@pytest.mark.parametrize("mode", ["e4m3", "e5m2"])
+def test_automatic_rows_per_thread_short_fp8(mode):
+    # 16-point FP8 rows: two rows per thread from 8 one-row workgroups per CU
+    # on, with the bits of either setting on both sides
+    need_gpu()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    line = 8 * cus * 256 - 255  # the first row count of 8 workgroups per CU
+    x = upload(0.125 * scenes.gaussian_rows(5, 97, 16), mode).repeat(line // 97 + 1, 1, 1)
+    for rows, two in ((line - 1, False), (line, True)):
+        announce(f"automatic rows per thread {mode} {rows}x16")
+        auto, plan, xr = api.FFTPlan(16, rows, mode), api.FFTPlan(16, rows, mode), x[:rows].contiguous()
+        want = auto.forward(xr)
+        assert any("row_kernel_rr" in k for k in kernels_of(lambda: auto.forward(xr))) == two
+        for rr in (1, 2):
+            plan.set_tuning_ex(1, 0, rr, 0)
+            assert torch.equal(plan.forward(xr), want)
