@@ -784,12 +784,21 @@ int fft_autotune_sets(bfp_plan p, int op, const void *const *ins, void *const *o
   if (p->kind == 0 && op == 2 && !filter) return fail(BFP_EINVAL, "compression needs a filter");
   std::vector<bfp_tuning> cands;
   if (p->kind == 1) {
-    // resident grids (the persistent loop over the work queue), then larger
-    // ones, up to one workgroup per tile, whose extra workgroups the
-    // hardware dispatches as resident ones finish
-    for (int b = 1; b <= p->uneven_max_bpc; ++b) cands.push_back({0, b, 1, 0});
+    // the default (one workgroup per tile, also beyond 64 tiles per CU, or the
+    // resident grid), resident grids (the persistent loop over the work queue),
+    // then larger ones, whose extra workgroups the hardware dispatches as
+    // resident ones finish; of the candidates that are the same launch (as many
+    // workgroups, or one per tile) the first
+    std::vector<int> bpcs = {0}, grids;
+    for (int b = 1; b <= p->uneven_max_bpc; ++b) bpcs.push_back(b);
     for (int b : {4, 8, 16, 32, 64})
-      if (b > p->uneven_max_bpc) cands.push_back({0, b, 1, 0});
+      if (b > p->uneven_max_bpc) bpcs.push_back(b);
+    for (int b : bpcs) {
+      const int g = std::min(bfp::uneven_grid(p, b), std::max(p->n_items, 1));
+      if (std::find(grids.begin(), grids.end(), g) != grids.end()) continue;
+      grids.push_back(g);
+      cands.push_back({0, b, 1, 0});
+    }
   } else {
     // engine x persistent grid x rows per thread x radix plan (the
     // matrix-core kernels take one row per workgroup and plan 0)

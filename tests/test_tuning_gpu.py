@@ -305,3 +305,23 @@ def test_automatic_rows_per_thread_short_fp8(mode):
         for rr in (1, 2):
             plan.set_tuning_ex(1, 0, rr, 0)
             assert torch.equal(plan.forward(xr), want)
+
+
+def test_uneven_autotune_keeps_the_default_where_it_is_the_same_launch():
+    # a batch of no more tiles than CUs has one launch, the default's; one
+    # beyond 64 tiles per CU (the largest explicit grid) has the default, one
+    # workgroup per tile, among its candidates, and any pick gives the same bits
+    need_gpu()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    announce("uneven autotune small and beyond 64 tiles per CU")
+    small = api.UnevenPlan(np.full(20, 10, np.int32), np.zeros(20, np.uint8), "fp16")
+    x = torch.zeros((small.total, 2), dtype=torch.float16, device="cuda")
+    small.set_tuning(0, 2)
+    assert small.autotune_on(0, x, torch.empty_like(x), reps=2) > 0 and small.get_tuning()[1] == 0
+    log2n = np.full(64 * cus + 16, 14, np.int32)
+    plan = api.UnevenPlan(log2n, np.zeros(log2n.size, np.uint8), "fp16")
+    x = torch.randn((plan.total, 2), device="cuda").half()
+    y, out = plan.execute(x), torch.empty_like(x)
+    assert plan.autotune_on(0, x, out, reps=2) > 0
+    assert plan.get_tuning()[1] in (0, 1, 2, 4, 8, 16, 32, 64)
+    assert torch.equal(plan.execute(x), y)
