@@ -23,20 +23,25 @@ namespace {
 
 // blocks_per_cu = kAutoBpc: the fused compression of pure FP16 up to n = 4096
 // runs the pipelined kernel on a persistent grid:
-//  - n = 4096: 5 workgroups per CU, as many as its registers let reside (1531
-//    rows 14.2 us against 15.3 at 3 per CU, 2048 rows 16.6 against 16.8 and
-//    17.3 at 8), and 8 where the rows outlast two rounds of those (4096 rows
-//    30.0 against 30.2 at 5 and 31.9 at 3, 3000 rows 24.1, 24.7, 26.2); 3 for
-//    the transposed store, whose XCD-aware row order wants few rows in flight
-//    (a 4096 x 4096 frame with the fused corner turn: 156 us at 3, 166 us at
-//    8);
+//  - n = 4096: 5 workgroups per CU, as many as the registers of the one-buffer
+//    kernel let reside (1531 rows 14.2 us against 15.3 at 3 per CU, 2048 rows
+//    16.6 against 16.8 and 17.3 at 8), and 8 where the rows outlast two rounds
+//    of those (4096 rows 30.0 against 30.2 at 5 and 31.9 at 3, 3000 rows 24.1,
+//    24.7, 26.2).  The variants of the two-buffer kernel (FP32 output,
+//    migration, adaptive, naive, output phase), of which 4 reside, take the same
+//    grid: at 3, 4 and 5 per CU 15.3, 13.1, 15.4 us with FP32 output and 16.1,
+//    14.5, 16.3 with migration (1531 rows), 17.8, 18.0, 18.0 and 19.9, 19.3, 18.1
+//    (2048 rows), adaptive 21.1, 21.8, 20.5; at 3 and 8 37.8, 36.6 and 37.1, 32.9
+//    (4096 rows).  3 for the transposed store, whose XCD-aware row order wants
+//    few rows in flight (a 4096 x 4096 frame with the fused corner turn: 156 us
+//    at 3, 166 us at 8);
 //  - n = 512, 8 values per thread: 16 (16384 rows 14.7 against 16.8 us at 3);
 //  - n = 256, 1024, 2048: 3 (4096 rows of 2048 17.0 against 17.2 us at 5, 8192
 //    of 1024 16.1 against 16.3).
 // Every other operation takes one workgroup per row group (the single
-// transforms are faster at full occupancy, and the FP32 image with its
-// entropy sums, 4096 x 4096, takes 75.5 against 79 us on one round of
-// resident workgroups).
+// transforms are faster at full occupancy, and the image with its entropy sums,
+// 4096 x 4096, takes 81.7 us in FP32 and 63.7 with FP16 storage either way: 82.6
+// and 63.4 on one round of resident workgroups, 2 and 3 per CU).
 constexpr int kAutoBpc = -1;
 
 int effective_bpc(const bfp_plan_s *p, int op, int rows, unsigned flags) {

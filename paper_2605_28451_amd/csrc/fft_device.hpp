@@ -519,10 +519,9 @@ __device__ __forceinline__ void st_stream_g(global_ptr<T> p, T v) {
 // nontemporal stores pass by, and no dirty lines are left to write back at the
 // kernel's end, as plain stores leave them.  A forward and an inverse of
 // 16384 x 4096 FP16: 161 against 182 us with nontemporal and 163 with plain
-// spectrum stores (2047 x 16384: 97, 104, 97; the forward transform by
-// itself, streaming, 91, 90, 94).  The inverse's own output, the end of a
-// chain, is better not kept (178 us), nor is the uneven batch's (156 against
-// 147 us).
+// spectrum stores (the forward transform by itself, streaming, 91, 90, 94).
+// The inverse's own output, the end of a chain, is better not kept (178 us),
+// nor is the uneven batch's (6% more time).
 template <class T>
 __device__ __forceinline__ void st_kept_g(global_ptr<T> p, T v) {
   static_assert(sizeof(T) == 2 || sizeof(T) == 4 || sizeof(T) == 8, "unsupported element size");
