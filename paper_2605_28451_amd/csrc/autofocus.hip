@@ -232,6 +232,9 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) phase_grad_kernel
   typedef Engine<ModeFP32, LOG2N, PLAN> EN;
   constexpr int E = G::E, T = G::T, N = G::N;
   constexpr int ROWS = G::TPW * RR;
+  // the block shift left to the second transform's first level, but at 1024
+  // threads, where it would spill (128 registers, 12 bytes of scratch)
+  constexpr bool kFold = G::WG < 1024;
   __shared__ c32 lds_all[NB * ROWS * G::LDS_N];
   // one transform per workgroup for N >= 4096: keep the row index uniform
   const int local = G::TPW == 1 ? 0 : (int)(threadIdx.x / T);
@@ -282,9 +285,13 @@ __global__ void __launch_bounds__((Geometry<LOG2N, PLAN>::WG)) phase_grad_kernel
 #pragma unroll
       for (int e = 0; e < E; ++e)  // adjoint: conj(H_a), then the block shift
 #pragma unroll
-        for (int q = 0; q < RR; ++q) v[q][e] = fold_in<LOG2N, E>(cmul(v[q][e], cconj(to_c32(h[e]))), e);
+        for (int q = 0; q < RR; ++q) {
+          const c32 z = cmul(v[q][e], cconj(to_c32(h[e])));
+          v[q][e] = kFold ? fold_in<LOG2N, E>(z, e) : conj_pow2<LOG2N>(z);
+        }
     }
-    EN::template run_rr<false, RR, NB>(v, buf, xch, tw, t, fold_leaf<c32, LOG2N>());
+    if constexpr (kFold) EN::template run_rr<false, RR, NB>(v, buf, xch, tw, t, fold_leaf<c32, LOG2N>());
+    else EN::template run_rr<false, RR, NB>(v, buf, xch, tw, t);
     c32 p[E];
     load_row<G, false>(p, ph, 0, ti);
 #pragma unroll
